@@ -308,19 +308,35 @@ hipError_t dispatch_tile(const GemmArgsBF16& a, GemmBF16Tile tile, hipStream_t s
 }  // namespace
 
 GemmBF16Tile pick_gemm_bf16_tile(GemmBF16Kind kind, int Mmax, int N, int K) {
-  // Measured on MI355X (microseconds per call, ~983K rows unless noted):
-  // in_proj (RMSNorm, N = 1024, K = 256) row panels 923 vs 1489 for the best
-  // tile, and at 492K rows 128-row panels (whole-line bf16 stores) 448 vs
-  // 496 for 256-row ones; gathered input Linear (N = 256, K = 164) 128-row
-  // panels 376 vs 391 for 256-row ones and 591 for the best tile; out_proj
-  // (K = 512, no panel) 128x128 629; x_proj (N = 48) 64x64 227. At ~15K rows
-  // (distillation) 128x64 wins for N <= 256 (7.2 vs 9.4 at N = 128, 11.9 vs
-  // 13.5 at 256).
-  if (N <= 64) return kB64x64;
-  if (K <= 256 && Mmax >= 131072 && kind != kF32toF32 && kind != kF32ResidF32)
-    return kind == kInputF32toF32 || kind == kNormF32toBF16 || kind == kBF16toBF16 ? kBPanel128 : kBPanel;
-  if (Mmax < 131072 && N <= 256) return kB128x64;
-  return kB128x128;
+  // Measured on MI355X (microseconds per call; rows: those with data, which
+  // Mmax = B * L exceeds by the padding, 1.67x at lengths U{L/5..L}). All tiles
+  // give the same bits; panels sum a row in another order. Below Mmax = 40,960,
+  // where a small model's training results would move with that order and
+  // panels gain nothing in a distillation step (1,265 us a pass against 1,258),
+  // tiles stay.
+  // Gathered input Linear (K = 164): N = 256, 1,000 rows 5.7 with 64x64 (8.2 with
+  // 128x64, 10.3 with 128x128), 10,000 9.4 (11.9, 12.7), 20,000 13.3 (15.9, 17);
+  // 128-row panels 21 vs 23.5 at 40,000 rows, 23.3 vs 33.5 at 61,600, 376 vs 591
+  // (391 for 256-row panels) at 983K.
+  // bf16 C, K <= 256 (in_proj N = 1024, K = 256): 64x64 while its tiles fit on
+  // the chip about once (1,000 rows 6.0 vs 6.8 for 64x128 and 9.5 for 128x128),
+  // then 64x128 (4,000 rows 9.1 vs 10.6 and 10.5; 10,000 17.7 vs 21 and 21),
+  // 128x128 (15,000 25.1 vs 25.9 for 64x128; 20,000 31.0 vs 32.4), 128-row panels
+  // (40,000 42.5 vs 54; 61,600 50 vs 82; 983K 896 vs 1489).
+  // Residual out_proj (no panel, K = 512): 64x64 up to 100,000 rows (10.8 vs 12.1
+  // for 128x64 at 10,000, 55 vs 57 and 66 for 128x128 at 100,000), 128x128
+  // above (99 vs 114 at 160,000). x_proj (N = 48) 64x64. The backward's fp32
+  // data gradients 64x64 at ~15,000 rows (8.3 vs 9.6 for 128x64 at N = 256, K =
+  // 128 with the residual, 10.2 vs 10.5 at N = 128, K = 512), 128x64 from 31,000
+  // (15.3 vs 13.5, 15.5 vs 15.0).
+  const bool bf16_out = kind == kNormF32toBF16 || kind == kBF16toBF16;
+  const bool f32_grad = kind == kF32toF32 || kind == kF32ResidF32;
+  if (N <= 64 && !(bf16_out || kind == kInputF32toF32)) return kB64x64;
+  if (K <= 256 && (bf16_out || kind == kInputF32toF32) && Mmax >= 40960) return kBPanel128;
+  if (bf16_out) return (int64_t)Mmax * N <= 1024 * 64 * 64 ? kB64x64 : Mmax < 24576 ? kB64x128 : kB128x128;
+  if (f32_grad) return Mmax < 32768 && N <= 256 ? kB64x64 : Mmax < 131072 && N <= 256 ? kB128x64 : kB128x128;
+  if (K <= 256 && Mmax >= 262144) return kBPanel;
+  return N <= 256 && Mmax < 262144 ? kB64x64 : kB128x128;
 }
 
 hipError_t launch_gemm_bf16(const GemmArgsBF16& a, GemmBF16Kind kind, int tile, hipStream_t s) {

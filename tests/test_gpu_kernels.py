@@ -318,6 +318,42 @@ def test_gemm_bf16_variants(kind, tile):
     assert np.all(err <= bound + 1e-30), (kind, tile, float(np.max(err / (bound + 1e-30))))
 
 
+@pytest.mark.parametrize("M", [1, 4096, 4097, 24575, 24576, 40959, 40960])
+@pytest.mark.parametrize("kind,N,K,panel", [("norm", 1024, 256, 40960), ("gather", 256, 164, 40960),
+                                            ("f32a", 256, 128, None), ("resid", 256, 512, None)])
+def test_gemm_bf16_model_tiles_keep_the_bits(kind, N, K, panel, M):
+    """Around each size where the model's tile choice changes: the chosen
+    kernel gives the bits of the 128x128 tiles, or of the 128-row panels where
+    those are chosen."""
+    print(f"gemm_bf16 model tile kind={kind} M={M}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    A = torch.randn(M, K, generator=g, device="cuda")
+    W = torch.zeros(N, (K + 7) // 8 * 8, dtype=torch.bfloat16, device="cuda")
+    W[:, :K] = torch.randn(N, K, generator=g, device="cuda").bfloat16()
+    kw = {}
+    if kind == "norm":
+        kw = dict(kind=tb.GEMM_BF16_NORM, gain=torch.rand(K, generator=g, device="cuda") + 0.5)
+    elif kind == "gather":
+        A = A.view(M, 1, K)
+        kw = dict(kind=tb.GEMM_BF16_GATHER, bias=torch.randn(N, generator=g, device="cuda"),
+                  offs=torch.arange(M + 1, dtype=torch.int32, device="cuda"))
+    elif kind == "resid":
+        A = A.bfloat16()
+        kw = dict(kind=tb.GEMM_BF16_RESID)
+    else:
+        kw = dict(kind=tb.GEMM_BF16_F32A)
+    start = torch.randn(M, N, generator=g, device="cuda")
+
+    def run(tile):
+        out = start.clone() if kind == "resid" else None
+        return tb.gemm_bf16(A, W, out=out, tile=tile, **kw)
+
+    same_as = 8 if panel is not None and M >= panel else 0
+    a, b = run(-1), run(same_as)
+    torch.cuda.synchronize()
+    assert torch.equal(a, b)
+
+
 def test_gemm_bf16_panel_rejects_unaligned_rows():
     """The row-panel tile stores 16-byte row segments: bf16 rows of 196
     columns (392 bytes) are refused when it is asked for explicitly, and the
