@@ -8,16 +8,14 @@
 // equal to it are gathered and bitonic-sorted in LDS by (key descending,
 // index ascending).
 //
-// RDU selection: the greedy loop of Alg. 1, one iteration per selected
-// program, on the device (the host only enqueues): a grid pass updates each
-// candidate's distance to the labeled set with the last selected program
-// (Eq. (1) kept as a running minimum), computes t_s = f d_s + u_s with the
-// variance of Eq. (2)-(3) from running sums, and reduces the argmax; a
-// one-workgroup pass labels the winner. A candidate whose operator type has
-// used its budget can never be labeled, so it is masked out as soon as that
-// happens; Alg. 1 drops such candidates one at a time when they come up as
-// the argmax, which leaves the same sequence of labeled programs. fp64
-// throughout (the normalised predictions, distances, sums and t_s).
+// RDU selection: the greedy loop of Alg. 1, one launch per selected program
+// (the host only enqueues), over the whole pool or over the short list of
+// candidates that can win: see rdu_score_kernel. A candidate
+// whose operator type has used its budget can never be labeled, so it is
+// masked out as soon as that is seen; Alg. 1 drops such candidates one at a
+// time when they come up as the argmax, which leaves the same sequence of
+// labeled programs. fp64 throughout (the normalised predictions, distances,
+// sums and t_s).
 #include "common.h"
 #include "kernels.h"
 
@@ -164,8 +162,18 @@ struct RduState {
   int last;          // the last selected program (-1: none yet)
   int done;
   int n_select;
-  unsigned arrived;  // blocks of the current grid pass that have parked their partial
-  int pad_[2];
+  unsigned arrived;  // blocks of the current launch that have parked their partial
+  int ver;           // labeled programs the whole pool's distances include
+  int nact;          // candidates collected for the short list
+  int active;        // this launch runs on the short list
+  int collect;       // this launch, over the whole pool, collects those with t_s >= cut
+  int spare;         // launches that may still come to nothing
+  int pad_;
+  double cut;            // the short list's bound
+  double cut_S1, cut_S2; // S1, S2 and M when it was collected
+  int cut_M;
+  int run;               // selections made from it
+  double next_cut;       // the bound the last pass over the whole pool suggests
 };
 
 struct Best {
@@ -179,25 +187,6 @@ __device__ __forceinline__ bool better(double t, int i, double bt, int bi) {
 
 __device__ __forceinline__ double fhat(const float* s, int i, const RduState& st) {
   return st.range > 0.0 ? ((double)s[i] - st.lo) / st.range : 0.0;
-}
-
-// block argmax of (t, i), lower index on ties; result in thread 0
-__device__ Best block_best(double t, int i, double* st, int* si) {
-  st[threadIdx.x] = t;
-  si[threadIdx.x] = i;
-  __syncthreads();
-  for (int o = kST / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) {
-      const double t2 = st[threadIdx.x + o];
-      const int i2 = si[threadIdx.x + o];
-      if (i2 >= 0 && better(t2, i2, st[threadIdx.x], si[threadIdx.x])) {
-        st[threadIdx.x] = t2;
-        si[threadIdx.x] = i2;
-      }
-    }
-    __syncthreads();
-  }
-  return Best{st[0], si[0]};
 }
 
 // per block: min and max of the scores, and a histogram of operator types
@@ -240,33 +229,60 @@ __global__ __launch_bounds__(kST) void rdu_zero_kernel(int n, int* __restrict__ 
   for (int i = blockIdx.x * kST + threadIdx.x; i < n; i += gridDim.x * kST) a[i] = 0;
 }
 
+// Histogram, over a sample of the pool, of how far t_s is above the smallest
+// u_s: bins of an eighth of a power of two, from 2^-40 up.
+constexpr int kHistBins = 42 * 8, kHistFirst = (1023 - 40) * 8;
+constexpr int kHistEvery = 32;  // one candidate in so many: one of four in every eighth block
+__device__ __forceinline__ int hist_bin(double t) {
+  const int b = (int)((uint64_t)__double_as_longlong(t) >> 49) - kHistFirst;
+  return t > 0.0 ? max(0, min(b, kHistBins - 1)) : 0;
+}
+__device__ __forceinline__ double u_min(double S1, double S2, double inv) {
+  // u = (inv - inv^2) f^2 - 2 S1 inv^2 f + S2 inv - (S1 inv)^2, f in [0, 1]
+  const double a = inv - inv * inv, f = a > 0.0 ? fmin(S1 * inv * inv / a, 1.0) : 1.0;
+  const double mu = (f + S1) * inv;
+  return (f * f + S2) * inv - mu * mu;
+}
+__device__ __forceinline__ double hist_edge(int b) {
+  return __longlong_as_double((long long)((uint64_t)(b + kHistFirst) << 49));
+}
+
 // one block: normalisation, budgets, sums over the initial labeled set
 __global__ __launch_bounds__(kST) void rdu_setup_kernel(int N, const float* __restrict__ s, int n_ops,
                                                         const int* __restrict__ init, int n_init, int n_select,
                                                         const float* __restrict__ mm, int nmm,
                                                         const int* __restrict__ opcount,
                                                         double* __restrict__ budget, int* __restrict__ sel,
+                                                        int spare, int* __restrict__ hist,
                                                         RduState* __restrict__ state) {
   __shared__ double r1[kST], r2[kST];
   __shared__ int rc[kST];
-  __shared__ double slo, srange;
-  if (threadIdx.x == 0) {
-    float mn = mm[0], mx = mm[1];
-    for (int b = 1; b < nmm; ++b) {
+  __shared__ float smn[kST], smx[kST];
+  {
+    float mn = INFINITY, mx = -INFINITY;
+    for (int b = threadIdx.x; b < nmm; b += kST) {
       mn = fminf(mn, mm[2 * b]);
       mx = fmaxf(mx, mm[2 * b + 1]);
     }
-    slo = (double)mn;
-    srange = (double)mx - (double)mn;
+    smn[threadIdx.x] = mn;
+    smx[threadIdx.x] = mx;
   }
   __syncthreads();
+  for (int o = kST / 2; o > 0; o >>= 1) {
+    if ((int)threadIdx.x < o) {
+      smn[threadIdx.x] = fminf(smn[threadIdx.x], smn[threadIdx.x + o]);
+      smx[threadIdx.x] = fmaxf(smx[threadIdx.x], smx[threadIdx.x + o]);
+    }
+    __syncthreads();
+  }
   RduState st{};
-  st.lo = slo;
-  st.range = srange;
+  st.lo = (double)smn[0];
+  st.range = (double)smx[0] - (double)smn[0];
   for (int o = threadIdx.x; o < n_ops; o += kST) {
     budget[o] = (double)n_select * (double)opcount[o] / (double)N;
     sel[o] = 0;
   }
+  for (int o = threadIdx.x; o < kHistBins; o += kST) hist[o] = 0;
   double a1 = 0.0, a2 = 0.0;
   int c = 0;
   for (int j = threadIdx.x; j < n_init; j += kST) {
@@ -298,6 +314,7 @@ __global__ __launch_bounds__(kST) void rdu_setup_kernel(int N, const float* __re
     st.last = -1;
     st.n_select = n_select;
     st.done = (n_select <= 0 || rc[0] == 0) ? 1 : 0;
+    st.spare = spare;
     *state = st;
   }
 }
@@ -352,23 +369,32 @@ __global__ __launch_bounds__(kST) void rdu_dinit_sorted_kernel(int N, const floa
                                                                const int* __restrict__ n_valid,
                                                                const RduState* __restrict__ state,
                                                                double* __restrict__ d) {
+  __shared__ double v[kSortInit / 4];
   const RduState st = *state;
   const int m = *n_valid;
+  const bool lds = m <= kSortInit / 4;  // block-uniform
+  if (lds) {
+    for (int j = threadIdx.x; j < m; j += kST) v[j] = sorted[j];
+    __syncthreads();
+  }
+  auto nearest = [&](const double* q, double fi) {
+    int lo = 0, hi = m;  // first index with q[idx] >= fi
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (q[mid] < fi) lo = mid + 1; else hi = mid;
+    }
+    double best = INFINITY;
+    if (lo < m) best = fmin(best, fabs(fi - q[lo]));
+    if (lo > 0) best = fmin(best, fabs(fi - q[lo - 1]));
+    return best;
+  };
   for (int i = blockIdx.x * kST + threadIdx.x; i < N; i += gridDim.x * kST) {
     if (s[i] != s[i] || m == 0) {
       d[i] = s[i] != s[i] ? -1.0 : INFINITY;
       continue;
     }
     const double fi = fhat(s, i, st);
-    int lo = 0, hi = m;  // first index with sorted[idx] >= fi
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (sorted[mid] < fi) lo = mid + 1; else hi = mid;
-    }
-    double best = INFINITY;
-    if (lo < m) best = fmin(best, fabs(fi - sorted[lo]));
-    if (lo > 0) best = fmin(best, fabs(fi - sorted[lo - 1]));
-    d[i] = best;
+    d[i] = lds ? nearest(v, fi) : nearest(sorted, fi);
   }
 }
 
@@ -407,79 +433,236 @@ __global__ __launch_bounds__(kST) void rdu_mark_kernel(int N, const int* __restr
   }
 }
 
-// one iteration, grid pass: distances, masks, t_s, block argmax; the last
-// block to finish reduces the blocks' partials and labels the winner.
-// Candidates go four per thread per round, their loads issued together.
+// One selection. Over the whole pool it reads every candidate's distance,
+// type and prediction: 138 MB and 53 us for 8.65 M programs, 64 times. But from
+// one selection to the next a candidate's t_s = f d + u can rise only by what
+// u rises: d is a running minimum (Eq. (1)), and u (Eq. (2)-(3)) is one
+// quadratic in f, whose largest change over f in [0, 1] is known in closed
+// form. So a pass over the whole pool also collects the candidates with t_s >=
+// cut, and the next launches run on that short list alone: while the list's
+// best is at or above cut plus the rise since, no candidate outside it can
+// win. When it no longer is, the launch selects nothing and the next one
+// takes the whole pool again (at most `spare` times, then all of them do, so
+// that n_select + spare launches always suffice). The cut comes from a
+// histogram of a sample of t_s, for half the list's room; a list that
+// overflows is not used.
+// The arithmetic per candidate is the same in both, and ties go to the lower
+// index, so the selection is too. The call over 8.65 M programs with 1,024
+// initial ones, 64 selections: 3.62 ms with passes over the whole pool only,
+// 1.09 ms now (three such passes and 62 launches of 8 us on lists, bound by
+// the latency of a launch's chain of loads, block reductions and arrival).
 constexpr int kRduUnroll = 4;
+constexpr int kRduList = 32768;       // room of the short list
+constexpr double kRiseMargin = 1e-12;  // far above the rounding of u_s and of its change (a few 1e-16)
+
+constexpr int kRduHeld = 256 + kST * kRduUnroll;  // of them held in LDS by a block: 256 and a round's
+
+struct ListItem {
+  double f, d;
+  int i, op;
+};
+
+// block argmax of (t, i), lower index on ties, i < 0: none; every thread gets it
+__device__ __forceinline__ Best block_best(double t, int i, double* st, int* si) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const double t2 = __shfl_xor(t, o, 64);
+    const int i2 = __shfl_xor(i, o, 64);
+    if (i2 >= 0 && better(t2, i2, t, i)) {
+      t = t2;
+      i = i2;
+    }
+  }
+  __syncthreads();  // st, si are free
+  if ((threadIdx.x & 63) == 0) {
+    st[threadIdx.x >> 6] = t;
+    si[threadIdx.x >> 6] = i;
+  }
+  __syncthreads();
+  t = st[0];
+  i = si[0];
+#pragma unroll
+  for (int w = 1; w < kST / 64; ++w)
+    if (si[w] >= 0 && better(st[w], si[w], t, i)) {
+      t = st[w];
+      i = si[w];
+    }
+  return Best{t, i};
+}
+
+__device__ __forceinline__ double rdu_t(double f, double d, const RduState& st, double inv) {
+  const double mu = (f + st.S1) * inv;                 // Eq. (2)
+  const double u = (f * f + st.S2) * inv - mu * mu;    // Eq. (3), from the running sums
+  return f * d + u;
+}
+
+// The most that u_s rose, for any f in [0, 1], since the list was collected:
+// the change is a f^2 + b f + c, largest at an end, or at the vertex when it
+// opens downwards.
+__device__ __forceinline__ double u_rise(const RduState& st) {
+  const double v = 1.0 / (double)(st.M + 1), w = 1.0 / (double)(st.cut_M + 1);
+  const double a = (v - v * v) - (w - w * w);
+  const double b = -2.0 * (st.S1 * v * v - st.cut_S1 * w * w);
+  const double c = (st.S2 * v - st.S1 * st.S1 * v * v) - (st.cut_S2 * w - st.cut_S1 * st.cut_S1 * w * w);
+  double m = fmax(c, a + b + c);
+  if (a < 0.0 && b > 0.0 && b < -2.0 * a) m = fmax(m, c - b * b / (4.0 * a));
+  return m + kRiseMargin;
+}
+
+template <bool LIST>  // with the short list, else over the whole pool always
 __global__ __launch_bounds__(kST) void rdu_score_kernel(int N, const float* __restrict__ s,
                                                         const int* __restrict__ op, int n_ops,
                                                         const double* __restrict__ budget,
-                                                        int* __restrict__ sel, RduState* __restrict__ state,
-                                                        double* __restrict__ d, Best* __restrict__ part,
-                                                        int* __restrict__ out) {
-  __shared__ double bt[kST];
-  __shared__ int bi[kST];
-  __shared__ int am_last;
+                                                        int* __restrict__ sel, RduState* state,
+                                                        double* __restrict__ d, Best* part, ListItem* list,
+                                                        int* hist, int* out) {
+  __shared__ double bt[kST / 64];
+  __shared__ int bi[kST / 64];
+  __shared__ double sfl[LIST ? kST : 1];
+  __shared__ int sil[LIST ? kST : 1];
+  __shared__ int sh[LIST ? kHistBins : 1];
+  __shared__ ListItem held[LIST ? kRduHeld : 1];
+  __shared__ int nheld, flag;
+  const int tid = threadIdx.x;
   const RduState st = *state;
   if (st.done) return;
-  const double fl = st.last >= 0 ? fhat(s, st.last, st) : 0.0;
   const double inv = 1.0 / (double)(st.M + 1);
   double best_t = 0.0;
   int best_i = -1;
-  constexpr int U = kRduUnroll;
-  for (int i0 = blockIdx.x * kST * U + threadIdx.x; i0 < N; i0 += gridDim.x * kST * U) {
-    double dv[U];
-    int ov[U];
-    float sv[U];
-#pragma unroll
-    for (int k = 0; k < U; ++k) {
-      const int i = i0 + k * kST;
-      const bool ok = i < N;
-      dv[k] = ok ? d[i] : -1.0;
-      ov[k] = ok ? op[i] : -1;
-      sv[k] = ok ? s[i] : 0.f;
-    }
-#pragma unroll
-    for (int k = 0; k < U; ++k) {
-      const int i = i0 + k * kST;
-      double di = dv[k];
-      if (di < 0.0) continue;  // labeled, past the end, or its operator's budget is used up
-      const int o = ov[k];
-      if (o < 0 || o >= n_ops || (double)sel[o] >= budget[o]) {
-        d[i] = -1.0;
-        continue;
+  int blocks = gridDim.x;  // blocks that take part
+  if (LIST && st.active) {
+    blocks = min((int)gridDim.x, max(1, (st.nact + kST - 1) / kST));
+    if ((int)blockIdx.x >= blocks) return;
+    for (int q = blockIdx.x * kST + tid; q < st.nact; q += blocks * kST) {
+      ListItem it = list[q];
+      const double dn = it.i == st.last ? -1.0 : fabs(it.f - fhat(s, st.last, st));
+      if (it.d >= 0.0) {
+        if ((double)sel[it.op] >= budget[it.op]) it.d = -1.0;
+        else it.d = fmin(it.d, dn);
+        list[q].d = it.d;
       }
-      const double fi = st.range > 0.0 ? ((double)sv[k] - st.lo) / st.range : 0.0;
-      if (st.last >= 0) {
-        const double dn = fabs(fi - fl);  // Eq. (1) as a running minimum
-        if (dn < di) {
-          di = dn;
-          d[i] = dn;
+      const double t = rdu_t(it.f, it.d, st, inv);
+      if (it.d >= 0.0 && better(t, it.i, best_t, best_i)) {
+        best_t = t;
+        best_i = it.i;
+      }
+    }
+  } else {
+    // the labels this pass brings into the distances: those since the last
+    // one, the first kST of them from LDS (without the list, the last label)
+    const int np = LIST ? st.count - st.ver : min(st.count, 1), npl = min(np, kST);
+    const double last_f = !LIST && np ? fhat(s, st.last, st) : 0.0;
+    if constexpr (LIST) {
+      for (int b = tid; b < kHistBins; b += kST) sh[b] = 0;
+      if (tid < npl) {
+        sil[tid] = out[st.ver + tid];
+        sfl[tid] = fhat(s, sil[tid], st);
+      }
+      if (tid == 0) nheld = 0;
+      __syncthreads();
+    }
+    const double base = u_min(st.S1, st.S2, inv);
+    const bool sampled = (blockIdx.x & (kHistEvery / 4 - 1)) == 0;
+    // the block's held items to the list (as far as it has room; the count
+    // goes on, so an overfull list is noticed)
+    auto append = [&](int n) {
+      if (tid == 0 && n) flag = atomicAdd(&state->nact, n);
+      __syncthreads();
+      for (int q = tid; q < n; q += kST)
+        if (flag + q < kRduList) list[flag + q] = held[q];
+      __syncthreads();
+      if (tid == 0) nheld = 0;
+      __syncthreads();
+    };
+    constexpr int U = kRduUnroll;
+    static_assert(U == 4, "the sample takes one of a round's four");
+    for (int64_t j0 = (int64_t)blockIdx.x * kST * U; j0 < N; j0 += (int64_t)gridDim.x * kST * U) {
+      // every load at a clamped place and without a condition, so that a
+      // round's twelve, then its eight lookups by type, are in flight together
+      double dv[U], fv[U], bud[U];
+      int iv[U], ov[U], sc[U];
+      float sv[U];
+      bool low[U];
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        iv[k] = (int)min(j0 + k * kST + tid, (int64_t)N - 1);
+        dv[k] = d[iv[k]];
+        ov[k] = op[iv[k]];
+        sv[k] = s[iv[k]];
+      }
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const int o = min(max(ov[k], 0), n_ops - 1);
+        sc[k] = sel[o];
+        bud[k] = budget[o];
+      }
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        fv[k] = st.range > 0.0 ? ((double)sv[k] - st.lo) / st.range : 0.0;
+        low[k] = false;
+      }
+      for (int p = 0; p < np; ++p) {
+        const int il = !LIST ? st.last : p < npl ? sil[p] : out[st.ver + p];
+        const double fl = !LIST ? last_f : p < npl ? sfl[p] : fhat(s, il, st);
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+          const double dn = il == iv[k] ? -1.0 : fabs(fv[k] - fl);  // a labeled program is no candidate
+          if (dn < dv[k]) {
+            dv[k] = dn;
+            low[k] = true;
+          }
         }
       }
-      const double mu = (fi + st.S1) * inv;                 // Eq. (2)
-      const double u = (fi * fi + st.S2) * inv - mu * mu;   // Eq. (3), from the running sums
-      const double t = fi * di + u;
-      if (better(t, i, best_t, best_i)) {
-        best_t = t;
-        best_i = i;
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const int i = iv[k], o = ov[k];
+        if (dv[k] >= 0.0 && (o < 0 || o >= n_ops || (double)sc[k] >= bud[k])) {
+          dv[k] = -1.0;  // its operator's budget is used up
+          low[k] = true;
+        }
+        const bool in = j0 + k * kST + tid < N;
+        if (in && low[k]) d[i] = dv[k];
+        const bool cand = in && dv[k] >= 0.0;  // not labeled, masked or past the end
+        const double t = cand ? rdu_t(fv[k], dv[k], st, inv) : 0.0;
+        if (cand && better(t, i, best_t, best_i)) {
+          best_t = t;
+          best_i = i;
+        }
+        if constexpr (LIST) {
+          if (k == 0 && sampled && cand) atomicAdd(&sh[hist_bin(t - base)], 1);
+          if (st.collect && cand && t >= st.cut)
+            held[atomicAdd(&nheld, 1)] = ListItem{fv[k], dv[k], i, o};
+        }
       }
+      if (LIST && st.collect) {  // block-uniform
+        __syncthreads();
+        const int n = nheld;
+        if (n > kRduHeld - kST * kRduUnroll) append(n);
+        else __syncthreads();  // nheld is read before the next round adds to it
+      }
+    }
+    if constexpr (LIST) {
+      __syncthreads();
+      if (st.collect) append(nheld);
+      if (sampled)
+        for (int b = tid; b < kHistBins; b += kST)
+          if (sh[b]) atomicAdd(&hist[b], sh[b]);
     }
   }
   const Best b = block_best(best_t, best_i, bt, bi);
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
     part[blockIdx.x] = b;
     __threadfence();  // the partial is visible before the arrival is counted
-    am_last = atomicAdd(&state->arrived, 1u) == gridDim.x - 1;
+    flag = atomicAdd(&state->arrived, 1u) == (unsigned)blocks - 1;
   }
   __syncthreads();
-  if (!am_last) return;
+  if (!flag) return;
 
   // the last block: every partial is in; reduce them and label the winner
   __threadfence();
   double t = 0.0;
   int i = -1;
-  for (int q = threadIdx.x; q < (int)gridDim.x; q += kST) {
+  for (int q = tid; q < blocks; q += kST) {
     const Best pq = part[q];
     if (pq.i >= 0 && better(pq.t, pq.i, t, i)) {
       t = pq.t;
@@ -487,24 +670,82 @@ __global__ __launch_bounds__(kST) void rdu_score_kernel(int N, const float* __re
     }
   }
   const Best w = block_best(t, i, bt, bi);
-  if (threadIdx.x == 0) {
-    RduState ns = st;
-    ns.arrived = 0;
-    if (w.i < 0) {
-      ns.done = 1;
+  int edge = kHistBins;
+  if (LIST && !st.active) {
+    // the lowest bin edge that half the list's room would hold: a suffix sum
+    // over the bins, lane l of one wavefront taking per bins from the top down
+    for (int q = tid; q < kHistBins; q += kST) sh[q] = atomicExch(&hist[q], 0);
+    if (tid == 0) flag = kHistBins;
+    __syncthreads();
+    if (tid < 64) {
+      constexpr int per = (kHistBins + 63) / 64;
+      int own[per], sum = 0;
+#pragma unroll
+      for (int r = 0; r < per; ++r) {
+        const int q = kHistBins - 1 - (tid * per + r);
+        sum += q >= 0 ? sh[q] : 0;
+        own[r] = sum;
+      }
+      int before = sum;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(before, o, 64);
+        if (tid >= o) before += v;
+      }
+      before -= sum;
+#pragma unroll
+      for (int r = 0; r < per; ++r) {
+        const int q = kHistBins - 1 - (tid * per + r);
+        if (q >= 0 && (before + own[r]) * (int64_t)kHistEvery <= kRduList / 2) atomicMin(&flag, q);
+      }
+    }
+    __syncthreads();
+    edge = flag;
+  }
+  if (tid == 0) {
+    state->arrived = 0;
+    int active = LIST && st.active, spare = st.spare;
+    const int nact = LIST ? atomicAdd(&state->nact, 0) : 0;  // as this launch left it
+    double next_cut = st.next_cut;
+    if (LIST && !active) {
+      state->ver = st.count;
+      state->next_cut = next_cut = u_min(st.S1, st.S2, inv) + hist_edge(min(edge, kHistBins - 1));
+    }
+    if (active && (w.i < 0 || !(w.t >= st.cut + u_rise(st)))) {
+      // a candidate outside the list may be better: the whole pool next
+      // (a list that served a single selection was not worth its launch: that
+      // counts four times)
+      spare = max(0, spare - (st.run < 2 ? 4 : 1));
+      active = 0;
+    } else if (w.i < 0) {
+      state->done = 1;
     } else {
       const double f = fhat(s, w.i, st);
-      out[ns.count] = w.i;
-      ns.count += 1;
-      ns.M += 1;
-      ns.S1 += f;
-      ns.S2 += f * f;
-      ns.last = w.i;
+      out[st.count] = w.i;
+      state->count = st.count + 1;
+      state->M = st.M + 1;
+      state->S1 = st.S1 + f;
+      state->S2 = st.S2 + f * f;
+      state->last = w.i;
       sel[op[w.i]] += 1;
-      d[w.i] = -1.0;
-      if (ns.count >= ns.n_select) ns.done = 1;
+      if (st.count + 1 >= st.n_select) state->done = 1;
+      state->run = st.run + 1;
+      if (LIST && st.collect && nact <= kRduList) {
+        active = 1;  // the list just collected holds every t_s >= cut
+        state->cut_S1 = st.S1;
+        state->cut_S2 = st.S2;
+        state->cut_M = st.M;
+        state->run = 0;
+      }
     }
-    *state = ns;
+    if constexpr (LIST) {
+      state->active = active;
+      state->spare = spare;
+      if (!active) state->nact = 0;
+      const bool collect = !active && spare > 0;
+      state->collect = collect;
+      if (collect) state->cut = next_cut;
+    }
   }
 }
 
@@ -620,6 +861,7 @@ size_t rdu_workspace_bytes(int N, int n_ops) {
   const int grid = std::min((N + kST - 1) / kST, kRduGrid);
   return al256(sizeof(RduState)) + al256((size_t)N * 8) + al256((size_t)n_ops * 8) +
          al256((size_t)(n_ops + 1) * 4) * 2 + al256((size_t)grid * 2 * 4) + al256((size_t)grid * sizeof(Best)) +
+         al256((size_t)kRduList * sizeof(ListItem)) + al256((size_t)kHistBins * 4) +
          al256((size_t)kSortInit * 8) + 256;
 }
 
@@ -642,6 +884,10 @@ hipError_t launch_rdu_select(int N, const float* s, const int* op, int n_ops, co
   p += al256((size_t)grid * 2 * 4);
   Best* part = reinterpret_cast<Best*>(p);
   p += al256((size_t)grid * sizeof(Best));
+  ListItem* list = reinterpret_cast<ListItem*>(p);
+  p += al256((size_t)kRduList * sizeof(ListItem));
+  int* hist = reinterpret_cast<int*>(p);
+  p += al256((size_t)kHistBins * 4);
   double* sorted = reinterpret_cast<double*>(p);
   p += al256((size_t)kSortInit * 8);
   int* n_valid = reinterpret_cast<int*>(p);
@@ -649,8 +895,17 @@ hipError_t launch_rdu_select(int N, const float* s, const int* op, int n_ops, co
   hipLaunchKernelGGL(rdu_zero_kernel, dim3(std::max(1, std::min((n_ops + kST) / kST, 64))), dim3(kST), 0, st,
                      n_ops + 1, opcount);
   hipLaunchKernelGGL(rdu_stats_kernel, dim3(grid), dim3(kST), 0, st, N, s, op, n_ops, mm, opcount);
+  // The short list pays where passes over the whole pool are long and the
+  // labeled set is dense enough in the pool for few candidates to be near the
+  // best t_s. Measured, us per selection with the list / without: 8.65 M
+  // programs with 1,024, 256, 128 and 64 initial ones 17 / 57, 40 / 57, 61 / 57
+  // and 63 / 57, 1 M with 64 and 32 13.6 / 28 and 24 / 28, 262,000 with 32 10.9 /
+  // 13.1, 100,000 with 64 9.6 / 9.6, 40,000 with 64 9.3 / 8.5.
+  const bool use_list = N > 4 * kRduList && n_init >= 32 && (int64_t)n_init * 40000 >= N;
+  // launches beyond n_select that may select nothing
+  const int spare = use_list ? n_select / 8 + 4 : 0;
   hipLaunchKernelGGL(rdu_setup_kernel, dim3(1), dim3(kST), 0, st, N, s, n_ops, init, n_init, n_select, mm, grid,
-                     opcount, budget, sel, state);
+                     opcount, budget, sel, spare, hist, state);
   if (n_init <= kSortInit) {
     hipLaunchKernelGGL(rdu_sort_init_kernel, dim3(1), dim3(1024), 0, st, N, s, init, n_init, state, sorted, n_valid);
     hipLaunchKernelGGL(rdu_dinit_sorted_kernel, dim3(grid), dim3(kST), 0, st, N, s, sorted, n_valid, state, d);
@@ -659,10 +914,14 @@ hipError_t launch_rdu_select(int N, const float* s, const int* op, int n_ops, co
   }
   if (n_init > 0)
     hipLaunchKernelGGL(rdu_mark_kernel, dim3((n_init + kST - 1) / kST), dim3(kST), 0, st, N, init, n_init, d);
-  const int sgrid = std::min((N + kST * kRduUnroll - 1) / (kST * kRduUnroll), kRduGrid);
-  for (int it = 0; it < n_select; ++it)
-    hipLaunchKernelGGL(rdu_score_kernel, dim3(sgrid), dim3(kST), 0, st, N, s, op, n_ops, budget, sel, state, d,
-                       part, out);
+  // a block's arrival costs more than a longer loop: 8.65 M programs 50.6 us a
+  // pass with 512 blocks, 53.0 with 768, 57.1 with 1,024; 1 M 19.6, 24.5, 28.3.
+  // With the list, whose few passes collect too: 1.19 ms a call with 512, 1.10
+  // with 1,024
+  const int sgrid = (int)std::min<int64_t>(((int64_t)N + kST * kRduUnroll - 1) / (kST * kRduUnroll), use_list ? kRduGrid : 512);
+  for (int it = 0; it < n_select + spare; ++it)
+    hipLaunchKernelGGL(use_list ? rdu_score_kernel<true> : rdu_score_kernel<false>, dim3(sgrid), dim3(kST), 0, st, N, s,
+                       op, n_ops, budget, sel, state, d, part, list, hist, out);
   hipLaunchKernelGGL(rdu_finish_kernel, dim3(1), dim3(kST), 0, st, n_select, state, out, count);
   return hipGetLastError();
 }

@@ -132,3 +132,25 @@ def test_rdu_select_large_initial_set():
     print(f"rdu N={N} init={n_init} select={n_sel}", flush=True)
     s, op, init = _rdu_case(N, n_ops, n_init, 78)
     _check_rdu_pool(s, op, n_ops, init, n_sel)
+
+
+@pytest.mark.parametrize("kind", ["random", "sorted", "coarse", "constant", "skewed_ops"])
+def test_rdu_select_short_list(kind):
+    """Pools large enough (over 131,072) for launches on a short list of
+    candidates: random scores; sorted ones (the best all in a few blocks);
+    scores on a grid of 64 values (ties, and lists that overflow); equal
+    scores; an operator type that takes most of the pool, so that budgets mask
+    listed candidates."""
+    N, n_ops, n_init, n_sel = 140_003, 6, 40, 14
+    print(f"rdu list {kind}", flush=True)
+    s, op, init = _rdu_case(N, n_ops, n_init, 200)
+    rng = np.random.default_rng(201)
+    if kind == "sorted":
+        s = np.sort(s)
+    elif kind == "coarse":
+        s = (np.round(s * 16) / 16).astype(np.float32)
+    elif kind == "constant":
+        s[:] = 0.25
+    elif kind == "skewed_ops":
+        op = np.where(rng.random(N) < 0.97, 0, 1 + rng.integers(0, n_ops - 1, N)).astype(np.int32)
+    _check_rdu_pool(s, op, n_ops, init, n_sel)
