@@ -190,7 +190,7 @@ tcl_status enqueue_block_f32(tcl_model* m, Timing& T, const std::string& tag, in
   const tcl_config& c = m->cfg;
   const int d = c.d_model, E = c.d_inner, N = c.d_state, R = c.dt_rank, XW = R + 2 * N;
   const int Mmax = B * L;
-  const int chunks = scan_chunks_for(B, E, L);
+  const int chunks = scan_small_wanted(B, E, N, R) ? 0 : scan_chunks_for(B, E, L);
   const auto& W = m->layers[l];
   GemmArgs gi;
   gi.A = H; gi.lda = d; gi.W = W.W_in_fold; gi.ldw = d; gi.C = xz; gi.ldc = 2 * E;
@@ -257,7 +257,7 @@ tcl_status run_score_part(tcl_model* m, int B, int L, const float* d_feats, cons
   float* xdbl = reinterpret_cast<float*>(ws + p.xdbl);
   const int d = c.d_model, E = c.d_inner, N = c.d_state, R = c.dt_rank, XW = R + 2 * N;
   const int Mmax = B * L;
-  const int chunks = scan_chunks_for(B, E, L);
+  const int chunks = scan_small_wanted(B, E, N, R) ? 0 : scan_chunks_for(B, E, L);
   Timing& T = m->timing;
 
   int* ord = reinterpret_cast<int*>(ws + p.ord);  // the programs longest first

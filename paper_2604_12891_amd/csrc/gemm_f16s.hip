@@ -516,9 +516,12 @@ hipError_t launch_f16s(const GemmArgs& a, const uint16_t* Wh, int ldwh, hipStrea
   const int grid = (a.Mmax + kBM - 1) / kBM;
   if (grid <= 0) return hipSuccess;
   // two workgroups per CU: with fewer than two panels per CU the columns are
-  // also split, up to 8 ways (each workgroup repeats its panel's prologue)
+  // also split, up to 8 ways (each workgroup repeats its panel's prologue), or
+  // up to 32 ways while that is one workgroup per CU: in_proj at 8 programs of
+  // up to 25 tokens 15.9 us with 8 ways, 12.8 with 16, 11.5 with 32; at 64 17.2,
+  // 14.5 and 16.5; at 128 18.2, 19.5 and 19.1
   const int nblk = (a.N + 31) / 32;
-  const int cs = std::max(1, std::min({8, nblk, 512 / grid}));
+  const int cs = std::max(1, std::min(nblk, std::max(std::min(8, 512 / grid), std::min(32, 256 / grid))));
   const dim3 g(grid, cs);
 #define TCL_F16S(KS)                                                                        \
   hipLaunchKernelGGL((gemm_f16s_kernel<KS, FL>), g, dim3(kNT), 0, s, a, Wh, ldwh); \
@@ -615,6 +618,7 @@ bool gemm_f16acc_supports(const GemmArgs& a, int flags) {
 
 hipError_t launch_gemm_f16acc(const GemmArgs& a, const uint16_t* Wh, int ldwh, int flags, hipStream_t s) {
   if (!gemm_f16acc_supports(a, flags) || ldwh < a.K || ldwh % 8) return hipErrorInvalidValue;
+  if (small_f16acc_wanted(a)) return launch_small_f16acc(a, Wh, ldwh, flags, s);
   switch (flags) {
     case 0: return launch_f16acc<0>(a, Wh, ldwh, s);
     case kBias: return launch_f16acc<kBias>(a, Wh, ldwh, s);

@@ -1200,6 +1200,7 @@ bool gemm_split_conv_supports(const GemmArgs& a, const ConvIn& cv, int d_conv) {
 
 hipError_t launch_gemm_split_conv(const GemmArgs& a, const ConvIn& cv, const uint16_t* Ws, int ldws, hipStream_t s) {
   if (!gemm_split_conv_supports(a, cv, 4)) return hipErrorInvalidValue;
+  if (small_conv_wanted(a)) return launch_small_conv(a, cv, Ws, ldws, s);
   const int grid = (a.Mmax + kWaves * 32 - 1) / (kWaves * 32);
   if (grid <= 0) return hipSuccess;
 #define TCL_SPLITCONV(KCH)                                                                                    \

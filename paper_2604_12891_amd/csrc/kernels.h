@@ -151,6 +151,14 @@ hipError_t launch_gemm_bf16_conv(const ConvArgsBF16& a, hipStream_t s);
 hipError_t launch_gemm_split_conv(const GemmArgs& a, const ConvIn& cv, const uint16_t* Ws, int ldws,
                                   hipStream_t s);
 
+// gemm_split_conv and gemm_f16acc for small batches (32-row workgroups, one
+// wavefront per 64 k): the launchers above hand over where *_wanted says so.
+// Same bits.
+bool small_conv_wanted(const GemmArgs& a);
+hipError_t launch_small_conv(const GemmArgs& a, const ConvIn& cv, const uint16_t* Ws, int ldws, hipStream_t s);
+bool small_f16acc_wanted(const GemmArgs& a);
+hipError_t launch_small_f16acc(const GemmArgs& a, const uint16_t* Wh, int ldwh, int flags, hipStream_t s);
+
 // bf16 GEMM: C = A W^T with A fp32 (converted while staged) or bf16, W bf16
 // ([N, ldw] row-major, zero-padded in K to a multiple of 8, ldw % 8 == 0),
 // C fp32 or bf16, fp32 accumulation. kRowNorm also scales A by gain[k]
@@ -278,6 +286,9 @@ hipError_t launch_scan_chunked(int B, int E, int N, int R, int chunks, const int
                                const float* b_dt, const float* A_log, const float* D, T* out,
                                hipStream_t s);
 int scan_chunks_for(int B, int E, int L);
+// Whether launch_scan runs a batch (without ysave and ckpt) on its small-batch
+// kernel, which then also takes the chunked scan's place.
+bool scan_small_wanted(int B, int E, int N, int R);
 
 // Final RMSNorm (optional) + masked mean-pool + Linear-ReLU-Linear head.
 // W1T is W1 transposed ([d, h]). Programs with invalid lengths get NaN.

@@ -495,6 +495,133 @@ __global__ __launch_bounds__(512) void scan_chunked_kernel(
   }
 }
 
+// ---------------------------------------------------------------- small-batch scan
+// The scan for batches too small to give every SIMD two wavefronts of
+// scan_kernel, where a token's chain through one wavefront (some 150 VALU
+// slots, and the loads it waits for) sets the time. A workgroup takes 64
+// channels of one program, kSmallTC tokens at a time:
+//  1. dt, dt u and the gate of every (token, channel), lane = channel, the
+//     tokens shared out over the four wavefronts;
+//  2. the recurrence, N / 4 states per lane: lane l of wavefront w holds states
+//     (N / 4)(l / 16) .. of channel 16 w + l % 16, so a token costs a wavefront
+//     about a quarter; the states go to LDS;
+//  3. y = C . s + D u and the gate, lane = channel again.
+// The operations and their order are scan_kernel's, so are the bits. The next
+// chunk's loads run during this one's recurrence. 8 programs of up to 25 tokens,
+// 512 channels: 14.2 -> 8.7 us; 64 programs, 128 channels: 17.9 -> 9.4; against the
+// chunked scan at L = 100, 64 programs, 55 -> 25, at L = 256, 16 programs, 65 -> 49.
+constexpr int kSmallTC = 16;
+template <typename T, int N, int R>
+__global__ __launch_bounds__(256) void scan_small_kernel(const int* __restrict__ offs, int E, const T* u,
+                                                         const float* __restrict__ xdbl, const T* __restrict__ z,
+                                                         int ldz, const float* __restrict__ W_dt,
+                                                         const float* __restrict__ b_dt,
+                                                         const float* __restrict__ A_log,
+                                                         const float* __restrict__ Dp, T* out,
+                                                         const int* __restrict__ ord) {
+  constexpr int XW = R + 2 * N, NL = N / 4, PT = kSmallTC / 4;
+  constexpr int XL = (kSmallTC * XW + 255) / 256;  // xdbl values per thread and chunk
+  typedef float states __attribute__((ext_vector_type(NL)));
+  __shared__ float sX[kSmallTC * XW];
+  __shared__ float sDt[kSmallTC][64], sDu[kSmallTC][64];
+  __shared__ states sS[kSmallTC][4][64];
+  const int CG = (E + 63) / 64;
+  const int slot = blockIdx.x / CG;
+  const int b = ord ? ord[slot] : slot;
+  const int e0 = (blockIdx.x % CG) * 64;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int e = e0 + lane;
+  const bool active = e < E;
+  const int ec = active ? e : 0;
+  const int base = offs[b], len = offs[b + 1] - base;
+  if (len <= 0) return;
+  const int j = wave * 16 + (lane & 15), g = lane >> 4;  // phase 2: channel of the 64, quarter of the states
+  const int e2 = e0 + j < E ? e0 + j : 0;
+
+  // a chunk's rows (those past its end read the program's last row, unused)
+  T un[PT], zn[PT];
+  float xn[XL];
+  auto load_chunk = [&](int t0) {
+#pragma unroll
+    for (int i = 0; i < PT; ++i) {
+      const int64_t r = base + min(t0 + wave + 4 * i, len - 1);
+      un[i] = u[r * E + ec];
+      zn[i] = z[r * ldz + ec];
+    }
+    const float* src = xdbl + (int64_t)(base + t0) * XW;
+    const int left = (len - t0) * XW - 1;
+#pragma unroll
+    for (int i = 0; i < XL; ++i) xn[i] = src[min((int)threadIdx.x + 256 * i, left)];
+  };
+  load_chunk(0);
+  float wdt[R], a2[NL], s[NL];
+#pragma unroll
+  for (int r = 0; r < R; ++r) wdt[r] = W_dt[ec * R + r];
+  const float bdt = b_dt[ec], Dv = Dp[ec];
+#pragma unroll
+  for (int n = 0; n < NL; ++n) {
+    a2[n] = -__builtin_amdgcn_exp2f(A_log[e2 * N + g * NL + n] * kLog2e) * kLog2e;
+    s[n] = 0.f;
+  }
+  for (int t0 = 0; t0 < len; t0 += kSmallTC) {
+    const int nt = min(kSmallTC, len - t0);
+    const int64_t r0 = base + t0;
+    float uv[PT], zv[PT];
+#pragma unroll
+    for (int i = 0; i < PT; ++i) {
+      uv[i] = to_f32(un[i]);
+      zv[i] = to_f32(zn[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < XL; ++i)
+      if ((int)threadIdx.x + 256 * i < kSmallTC * XW) sX[threadIdx.x + 256 * i] = xn[i];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < PT; ++i) {
+      const int t = wave + 4 * i;
+      if (t < nt) {  // wavefront-uniform
+        float v = bdt;
+#pragma unroll
+        for (int r = 0; r < R; ++r) v = fmaf(wdt[r], sX[t * XW + r], v);
+        const float dt = softplus(v);
+        sDt[t][lane] = dt;
+        sDu[t][lane] = dt * uv[i];
+      }
+    }
+    if (t0 + kSmallTC < len) load_chunk(t0 + kSmallTC);
+    __syncthreads();
+#pragma unroll 4
+    for (int t = 0; t < nt; ++t) {
+      const float dt = sDt[t][j], du = sDu[t][j];
+      const float* bc = &sX[t * XW + R + g * NL];
+      states st;
+#pragma unroll
+      for (int n = 0; n < NL; ++n) {
+        s[n] = fmaf(__builtin_amdgcn_exp2f(dt * a2[n]), s[n], du * bc[n]);
+        st[n] = s[n];
+      }
+      sS[t][g][j] = st;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < PT; ++i) {
+      const int t = wave + 4 * i;
+      if (t < nt && active) {
+        float y = 0.f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const states st = sS[t][q][lane];
+#pragma unroll
+          for (int n = 0; n < NL; ++n) y = fmaf(st[n], sX[t * XW + R + N + q * NL + n], y);
+        }
+        y = fmaf(Dv, uv[i], y);
+        st1(out + (r0 + t) * E + e, y * silu(zv[i]));
+      }
+    }
+    __syncthreads();  // sX is free
+  }
+}
+
 // ---------------------------------------------------------------- tail
 // PB programs per workgroup. Phase 1: each wavefront pools whole programs
 // (per token: RMSNorm statistics by a wavefront reduction, then accumulate
@@ -526,7 +653,46 @@ __global__ __launch_bounds__(256) void tail_kernel(int B, int L, int h, const in
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int b0 = blockIdx.x * kTailPB;
 
-  for (int p = wave; p < kTailPB; p += 4) {
+  if constexpr (kTailPB == 1) {
+    // one program: the wavefronts share its tokens' statistics, then thread k
+    // sums column k over the tokens in order (the same operations as below,
+    // a token's statistics no longer in the chain)
+    constexpr int TC = 64;
+    __shared__ float sRs[TC];
+    const int base = offs[b0], len = offs[b0 + 1] - base;
+    float acc = 0.f;
+    for (int t0 = 0; t0 < len; t0 += TC) {
+      const int nt = min(TC, len - t0);
+      const float* Hc = H + (int64_t)(base + t0) * DM;
+      if (final_norm) {
+#pragma unroll 4
+        for (int t = wave; t < nt; t += 4) {
+          float ss = 0.f;
+#pragma unroll
+          for (int i = 0; i < PL; ++i) {
+            const float v = Hc[(int64_t)t * DM + lane * PL + i];
+            ss = fmaf(v, v, ss);
+          }
+          ss = wave_sum(ss);
+          if (lane == 0) sRs[t] = 1.0f / sqrtf(ss / (float)DM + eps);
+        }
+      } else if (tid < nt) {
+        sRs[tid] = 1.f;
+      }
+      __syncthreads();
+      if (tid < DM) {
+#pragma unroll 8
+        for (int t = 0; t < nt; ++t) acc = fmaf(Hc[(int64_t)t * DM + tid], sRs[t], acc);
+      }
+      __syncthreads();
+    }
+    if (tid < DM) {
+      const float v = acc * (final_norm ? g_f[tid] : 1.f) * (len > 0 ? 1.0f / (float)len : 0.f);
+      sP[tid][0] = v;
+      if (pooled_out) pooled_out[(int64_t)b0 * DM + tid] = v;
+    }
+  }
+  for (int p = wave; kTailPB > 1 && p < kTailPB; p += 4) {
     const int b = b0 + p;
     float acc[PL];
 #pragma unroll
@@ -600,7 +766,7 @@ __global__ __launch_bounds__(256) void tail_kernel(int B, int L, int h, const in
     // W1 in batches of KB rows, the next batch loaded while the current one
     // is used (L2 latency, not the FMAs, bounds this loop); fully unrolled,
     // so the batches are fixed registers and no load is conditional
-    constexpr int KB = kTailPB > 4 ? 8 : 16;  // (more programs: more FMAs per row, fewer rows needed in flight)
+    constexpr int KB = kTailPB > 4 ? 8 : kTailPB > 1 ? 16 : 32;  // (more programs: more FMAs per row, fewer rows needed in flight)
     static_assert(DM % (2 * KB) == 0, "whole pairs of W1 batches");
     float wa[KB], wb[KB];
     auto load_w = [&](int k0, float* w) {
@@ -790,6 +956,13 @@ int scan_chunks_for(int B, int E, int L) {
   return c;
 }
 
+// Whether a batch gets the small-batch scan: up to 1,024 workgroups. At E = 512, L =
+// 25: 14.8 us vs 19.7 with 1,024 of them (bf16 14.1 vs 18.8), bf16 20.8 vs 19.2 with
+// 1,600; E = 256 22.9 vs 19.1 with 2,048.
+bool scan_small_wanted(int B, int E, int N, int R) {
+  return (int64_t)B * ((E + 63) / 64) <= 1024 && (N == 16 || N == 8) && (R == 4 || R == 8 || R == 16);
+}
+
 template <typename T>
 hipError_t launch_scan(int B, int E, int N, int R, const int* offs, const T* u, const float* xdbl,
                        const T* z, int ldz, const float* W_dt, const float* b_dt, const float* A_log,
@@ -797,6 +970,24 @@ hipError_t launch_scan(int B, int E, int N, int R, const int* offs, const T* u, 
   if (B <= 0) return hipSuccess;
   if (N != 16 && N != 8) return hipErrorInvalidValue;
   if (ckpt && (L <= 0 || reinterpret_cast<uintptr_t>(ckpt) % 16)) return hipErrorInvalidValue;
+  if (!ysave && !ckpt && scan_small_wanted(B, E, N, R)) {
+    const dim3 sg(B * ((E + 63) / 64));
+#define TCL_SCANS(NN, RR)                                                                                           \
+  case NN * 100 + RR:                                                                                               \
+    hipLaunchKernelGGL((scan_small_kernel<T, NN, RR>), sg, dim3(256), 0, s, offs, E, u, xdbl, z, ldz, W_dt, b_dt, A_log, \
+                       D, out, ord);                                                                                \
+    return hipGetLastError()
+    switch (N * 100 + R) {
+      TCL_SCANS(16, 4);
+      TCL_SCANS(16, 8);
+      TCL_SCANS(16, 16);
+      TCL_SCANS(8, 4);
+      TCL_SCANS(8, 8);
+      TCL_SCANS(8, 16);
+      default: return hipErrorInvalidValue;
+    }
+#undef TCL_SCANS
+  }
   const int nck = (L + kScanCkptTokens - 1) / kScanCkptTokens;
   const int cgroups = (E + kScanThreads - 1) / kScanThreads;
   const int grid = 8 * cgroups * ((B + 7) / 8);
@@ -849,9 +1040,12 @@ hipError_t tail_any(int B, int L, int d, int h, const int* offs, const int* leng
                     float* a1_out, int h2, const float* W3, const float* b3) {
   if (B <= 0) return hipSuccess;
   if (h <= 0 || h > 256 || h2 < 0 || h2 > 256) return hipErrorInvalidValue;
-  // 16 programs per workgroup share each W1 read; small batches use 4 so
-  // that there are enough workgroups to spread over the CUs
-  const int pb = B >= 8192 ? 16 : 4;
+  // 16 programs per workgroup share each W1 read; smaller batches use 4 so
+  // that there are enough workgroups to spread over the CUs, and the smallest
+  // one, whose tokens all four wavefronts share
+  // (8 programs of 25 tokens, d 256: 20.2 -> 12.5 us, 512: 23.0 -> 14.3, 1,024: 23.5
+  // -> 18.6, 1,500: 25.4 -> 26.3; 100 programs of 256 tokens: 112 -> 49)
+  const int pb = B >= 8192 ? 16 : B > 1024 ? 4 : 1;
   dim3 grid((B + pb - 1) / pb);
   const bool d3 = h2 > 0;
 #define TCL_TAIL(DD, PB)                                                                                  \
@@ -866,6 +1060,9 @@ hipError_t tail_any(int B, int L, int d, int h, const int* offs, const int* leng
     case 6416: TCL_TAIL(64, 16); break;
     case 12816: TCL_TAIL(128, 16); break;
     case 25616: TCL_TAIL(256, 16); break;
+    case 6401: TCL_TAIL(64, 1); break;
+    case 12801: TCL_TAIL(128, 1); break;
+    case 25601: TCL_TAIL(256, 1); break;
     case 6404: TCL_TAIL(64, 4); break;
     case 12804: TCL_TAIL(128, 4); break;
     case 25604: TCL_TAIL(256, 4); break;

@@ -868,3 +868,118 @@ def test_gemm_split32acc(M, N, K, mode):
     ref, bound = _split_ref(A, W, mode, bv, C0)
     err = np.abs(C.cpu().numpy() - ref)
     assert np.all(err <= bound + 1e-30), float(np.max(err / (bound + 1e-30)))
+
+
+@pytest.mark.parametrize("E,N", [(512, 48), (256, 40), (128, 24), (64, 64)])
+@pytest.mark.parametrize("tail", [0, 1, 31])
+def test_small_conv_matches_the_panels(E, N, tail):
+    """conv + x_proj of a small batch (32-row workgroups, one wavefront per 64
+    channels) against the 128-row panels, which a larger bound on the rows
+    gets: the same bits of u and of u W^T; whole, one-row and 31-row last
+    workgroups."""
+    rng = np.random.default_rng(E + N + tail)
+    lengths = np.concatenate([[1, 2, 3, 4, 0, 40, 31, 33, 1, 1, 29, 3], rng.integers(1, 41, 20)]).astype(np.int32)
+    lengths = np.append(lengths, (tail - int(lengths.sum())) % 32)
+    M = int(lengths.sum())
+    print(f"small conv E={E} N={N} M={M}", flush=True)
+    x = rng.standard_normal((M, 2 * E)).astype(np.float32)
+    w = rng.uniform(-0.5, 0.5, (E, 4)).astype(np.float32)
+    b = rng.uniform(-0.5, 0.5, E).astype(np.float32)
+    W = (rng.uniform(-1, 1, (N, E)) / np.sqrt(E)).astype(np.float32)
+    got = []
+    for rows in (M, 40000):
+        u, xdbl = tb.xproj_conv_f32(_dev(_offs(lengths), torch.int32), _dev(x), _dev(w), _dev(b), _dev(W), rows, E,
+                                    ldx=2 * E)
+        torch.cuda.synchronize()
+        got.append((u.cpu().numpy()[:M], xdbl.cpu().numpy()[:M]))
+    for p, q in zip(*got):
+        np.testing.assert_array_equal(p.view(np.uint32), q.view(np.uint32))
+    ref, bound = _split_ref(got[0][0], W, "plain")
+    err = np.abs(got[0][1] - ref)
+    assert np.all(err <= bound + 1e-30), float(np.max(err / (bound + 1e-30)))
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 64, 64), (33, 256, 512), (3328, 256, 512), (77, 100, 500), (200, 128, 128),
+                                   (65, 40, 256)])
+@pytest.mark.parametrize("mode", ["plain", "bias", "resid"])
+def test_small_f16acc_matches_the_panels(M, N, K, mode):
+    """The two-part fp16 product of a small batch against the panels, which the
+    same rows inside a larger batch get: the same bits, within the bound; rows
+    at 10^-28 .. 10^28 with 64-wide pieces of a row at magnitudes of their
+    own (the running scale drops), ragged M, N and K, up to the rule's limit."""
+    print(f"small f16acc mode={mode} M={M} N={N} K={K}", flush=True)
+    rng = np.random.default_rng(M + 7 * N + 19 * K + len(mode) + 31)
+    big = 416 * 32 * 64 // N + 33
+    A = rng.standard_normal((big, K)) * 10.0 ** rng.integers(-28, 29, size=(big, 1))
+    A *= np.repeat(10.0 ** rng.integers(-2, 3, size=(big, (K + 63) // 64)), 64, axis=1)[:, :K]
+    A[M // 2] = 0.0
+    A = A.astype(np.float32)
+    W = rng.standard_normal((N, K)).astype(np.float32)
+    bv = rng.standard_normal(N).astype(np.float32) if mode == "bias" else None
+    C0 = rng.standard_normal((big, N)).astype(np.float32)
+    got = []
+    for m in (M, big):
+        C = _dev(C0[:m])
+        tb.gemm_split(_dev(A[:m]), _dev(W), _dev(bv) if bv is not None else None, out=C, variant=6,
+                      epilogue=1 if mode == "resid" else 0)
+        torch.cuda.synchronize()
+        got.append(C.cpu().numpy()[:M])
+    np.testing.assert_array_equal(got[0].view(np.uint32), got[1].view(np.uint32))
+    ref, bound = _f16_ref(A[:M], W, "bias" if mode == "bias" else "plain", bv)
+    if mode == "resid":
+        ref = ref + C0[:M]
+        bound = bound + 2.0 ** -23 * np.abs(ref)
+    err = np.abs(got[0] - ref)
+    assert np.all(np.isfinite(got[0]))
+    assert np.all(err <= bound + 1e-300), float(np.max(err / (bound + 1e-300)))
+
+
+@pytest.mark.parametrize("R", [4, 8, 16])
+@pytest.mark.parametrize("L", [1, 15, 16, 17, 50])
+def test_small_scan_matches_the_general_scan(R, L):
+    """The small-batch scan (chunks of 16 tokens, four lanes per channel)
+    against scan_kernel: the same programs, first on their own, then followed
+    by as many of one token as it takes. The same bits."""
+    N, E, B = 16, 320, 9
+    print(f"small scan R={R} L={L}", flush=True)
+    rng = np.random.default_rng(R * 10 + L)
+    lengths = rng.integers(1, L + 1, size=B).astype(np.int32)
+    lengths[0] = L
+    many = np.concatenate([lengths, np.ones(1024, np.int32)])
+    M, rows = int(lengths.sum()), int(many.sum())
+    u = rng.standard_normal((rows, E)).astype(np.float32)
+    z = rng.standard_normal((rows, E)).astype(np.float32)
+    xdbl = (0.5 * rng.standard_normal((rows, R + 2 * N))).astype(np.float32)
+    par = [rng.uniform(-0.5, 0.5, (E, R)), np.log(np.expm1(np.exp(rng.uniform(np.log(1e-3), np.log(1e-1), E)))),
+           np.log(np.arange(1, N + 1))[None, :] + 0.3 * rng.standard_normal((E, N)), rng.standard_normal(E)]
+    out = []
+    for ln, m in ((lengths, M), (many, rows)):
+        o = torch.full((m, E), float("nan"), device="cuda")
+        tb.scan_f32(_dev(_offs(ln), torch.int32), _dev(u[:m]), _dev(xdbl[:m]), _dev(z[:m]),
+                    *[_dev(a.astype(np.float32)) for a in par], o)
+        torch.cuda.synchronize()
+        out.append(o.cpu().numpy()[:M])
+    np.testing.assert_array_equal(out[0].view(np.uint32), out[1].view(np.uint32))
+
+
+@pytest.mark.parametrize("shape,dtype", [(wl.TINY, "bf16"), (wl.D256, "f32"), (wl.PAPER_GPU, "f32")])
+@pytest.mark.parametrize("B", [1, 7, 130])
+def test_small_batches_keep_the_bits(shape, dtype, B):
+    """Scores of a small batch (the small-batch scan, conv, out_proj and tail)
+    are the bits of the same programs inside a batch of 2,100."""
+    L = 41
+    print(f"small batch B={B} {dtype}", flush=True)
+    rng = np.random.default_rng(B)
+    blob = wl.init_params(shape, rng, perturb=True)
+    if dtype == "bf16":
+        blob = wl.round_to_bf16(blob)
+    X, lengths = wl.make_inputs(2100, L, shape.F, 1, L, rng)
+    m = tb.CostModel(tb.config_from_shape(shape, dtype), blob)
+    Xd, Ld = torch.from_numpy(X).cuda(), torch.from_numpy(lengths).cuda()
+    whole = m.score(Xd, Ld)
+    part = m.score(Xd[:B].contiguous(), Ld[:B].contiguous())
+    torch.cuda.synchronize()
+    if dtype == "bf16":  # in_proj's panels, from 40,960 padded rows, sum a row's squares in another order
+        assert ((whole[:B] - part).abs() <= 2e-2 * whole.abs().max()).all()
+    else:
+        assert torch.equal(whole[:B], part)
