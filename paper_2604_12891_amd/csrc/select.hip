@@ -2,11 +2,11 @@
 // section 3 keeps the K best candidates of a tuning round) and the RDU
 // sampler's selection of programs to label (section 4, Alg. 1, Eq. (1)-(3)).
 //
-// Top-K: one workgroup of 1,024 threads per segment. Scores map to order-preserving 32-bit
-// keys (NaN below everything); a four-pass radix select over 8-bit digits
-// finds the K-th largest key; the items above it and the lowest-index items
-// equal to it are gathered and bitonic-sorted in LDS by (key descending,
-// index ascending).
+// Top-K: one workgroup of 1,024 threads per segment. Scores map to
+// order-preserving 32-bit keys (NaN below everything); a radix select finds a
+// key that at least K and not many more keys reach, and those are gathered and
+// ranked in LDS by (key descending, index ascending). Where too many keys
+// equal the K-th, the lowest-index ones are taken.
 //
 // RDU selection: the greedy loop of Alg. 1, one launch per selected program
 // (the host only enqueues), over the whole pool or over the short list of
@@ -53,104 +53,148 @@ __device__ __forceinline__ int block_prefix(bool flag, int* wsum, int* total) {
   return before + in_wave;
 }
 
-template <int P>  // P: power of two >= K
+// CAP: candidates gathered at most, >= K. Digits of 12, 10 and 10 bits, the
+// first alone when the K-th key's bin is short: with 4,096 scores and K = 64 it
+// holds some 60 keys (an eighth of a power of two), and what lies above and in
+// it fits the candidates. Each candidate's place is then the number of larger
+// ones. Up to kTKeys keys a thread stay in registers. 16 segments of about
+// 4,096, K = 64: 16.7 us with four 8-bit passes over memory and a bitonic sort,
+// 7.3 now: a launch, one round of loads and a dozen barriers. One segment of
+// 65,536, K = 64: 138 -> 27.
+constexpr int kTKeys = 8;
+template <int CAP>
 __global__ __launch_bounds__(kTK) void topk_kernel(const int* __restrict__ offs, const float* __restrict__ s,
                                                    int K, int* __restrict__ out) {
-  __shared__ int hist[kTK / 64][256];  // one histogram per wavefront (scores crowd a few top digits)
-  __shared__ int tot[4];
-  __shared__ uint64_t cand[P];
+  constexpr int kBins = 4096;
+  __shared__ __attribute__((aligned(16))) uint64_t cand[CAP];
+  __shared__ int hist[kBins];
+  __shared__ int tot[kTK / 64];
   __shared__ int wsum[kTK / 64];
-  __shared__ int sdig, sabove, cnt_gt;
+  __shared__ int sdig, sabove, scount, cnt;
   const int g = blockIdx.x;
   const int lo = offs[g];
   const int n = max(offs[g + 1] - lo, 0);
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int take = min(n, K);
 
-  for (int i = tid; i < P; i += kTK) cand[i] = 0ull;  // padding sorts last
-  if (tid == 0) cnt_gt = 0;
-  uint32_t kth = 0u;
-  int need_eq = take;  // items equal to kth to keep (all, when n <= K)
+  const bool regs = n <= kTKeys * kTK;  // block-uniform
+  uint32_t key[kTKeys];
+  if (regs) {
+#pragma unroll
+    for (int r = 0; r < kTKeys; ++r) key[r] = n > 0 ? score_key(s[lo + min(tid + r * kTK, n - 1)]) : 0u;
+  }
+  // f(key, index) of every key of this thread
+  auto visit = [&](auto f) {
+    if (regs) {
+#pragma unroll
+      for (int r = 0; r < kTKeys; ++r)
+        if (tid + r * kTK < n) f(key[r], tid + r * kTK);
+    } else {
+      for (int i0 = tid; i0 < n; i0 += kTKeys * kTK) {  // a round's loads together
+        float v[kTKeys];
+#pragma unroll
+        for (int r = 0; r < kTKeys; ++r) v[r] = s[lo + min(i0 + r * kTK, n - 1)];
+#pragma unroll
+        for (int r = 0; r < kTKeys; ++r)
+          if (i0 + r * kTK < n) f(score_key(v[r]), i0 + r * kTK);
+      }
+    }
+  };
+  auto code_of = [](uint32_t k, int i) { return ((uint64_t)k << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)i); };
+
+  if (tid == 0) cnt = 0;
+  uint32_t least = 0u;  // candidates: keys >= least
+  bool exact = true;    // they fit CAP
+  int krem = K;
   if (n > K) {
     uint32_t prefix = 0u, pmask = 0u;
-    int krem = K;
-    const int wave = tid >> 6;
-    for (int shift = 24; shift >= 0; shift -= 8) {
+    int above = 0;
+    exact = false;
+    for (int pass = 0; pass < 3 && !exact; ++pass) {
+      const int shift = pass == 0 ? 20 : pass == 1 ? 10 : 0, nb = pass == 0 ? kBins : 1024;
+      for (int b = tid; b < nb; b += kTK) hist[b] = 0;
       __syncthreads();
-      for (int b = tid; b < (kTK / 64) * 256; b += kTK) (&hist[0][0])[b] = 0;
+      visit([&](uint32_t k, int) {
+        if ((k & pmask) == prefix) atomicAdd(&hist[(k >> shift) & (nb - 1)], 1);
+      });
       __syncthreads();
-      for (int i = tid; i < n; i += kTK) {
-        const uint32_t key = score_key(s[lo + i]);
-        if ((key & pmask) == prefix) atomicAdd(&hist[wave][(key >> shift) & 255], 1);
-      }
-      __syncthreads();
-      // thread t < 256 takes digit 255 - t; an inclusive scan over threads is
-      // then the count of keys at or above that digit, and exactly one digit
-      // has that count reach krem while the digits above it stay below
-      int c = 0, incl = 0;
-      if (tid < 256) {
+      // thread t takes four digits from nb - 1 - 4 t down; a scan over threads
+      // gives the count of keys at or above each, and exactly one digit has
+      // that count reach krem while the digits above it stay below
+      int c[4], sum = 0;
 #pragma unroll
-        for (int w = 0; w < kTK / 64; ++w) c += hist[w][255 - tid];
-        incl = c;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-          const int v = __shfl_up(incl, o, 64);
-          if ((tid & 63) >= o) incl += v;
-        }
-        if ((tid & 63) == 63) tot[tid >> 6] = incl;
+      for (int r = 0; r < 4; ++r) {
+        const int d = nb - 1 - (4 * tid + r);
+        c[r] = d >= 0 ? hist[d] : 0;
+        sum += c[r];
       }
+      int incl = sum;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += v;
+      }
+      if (lane == 63) tot[wave] = incl;
       __syncthreads();
-      if (tid < 256) {
-        for (int w = 0; w < (tid >> 6); ++w) incl += tot[w];
-        if (incl >= krem && incl - c < krem) {
-          sdig = 255 - tid;
-          sabove = incl - c;
+      int at = incl - sum;
+#pragma unroll
+      for (int w = 0; w < kTK / 64; ++w) at += w < wave ? tot[w] : 0;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if (at < krem && at + c[r] >= krem) {
+          sdig = nb - 1 - (4 * tid + r);
+          sabove = at;
+          scount = c[r];
         }
+        at += c[r];
       }
       __syncthreads();
       krem -= sabove;
+      above += sabove;
       prefix |= (uint32_t)sdig << shift;
-      pmask |= 0xFFu << shift;
-    }
-    kth = prefix;
-    need_eq = krem;
-  }
-  __syncthreads();
-  // gather: every key above kth, then the first need_eq keys equal to it
-  int eq_base = 0;
-  for (int t0 = 0; t0 < n; t0 += kTK) {
-    const int i = t0 + tid;
-    const bool ok = i < n;
-    const uint32_t key = ok ? score_key(s[lo + i]) : 0u;
-    const uint64_t code = ((uint64_t)key << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)i);
-    const bool gt = ok && n > K && key > kth;
-    const bool eq = ok && (n <= K || key == kth);
-    if (gt) cand[atomicAdd(&cnt_gt, 1)] = code;
-    int tot;
-    const int r = block_prefix(eq, wsum, &tot);
-    if (eq && eq_base + r < need_eq) cand[(take - need_eq) + eq_base + r] = code;
-    eq_base += tot;
-  }
-  __syncthreads();
-  // bitonic sort, descending
-  for (int k = 2; k <= P; k <<= 1) {
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int i = tid; i < P; i += kTK) {
-        const int p = i ^ j;
-        if (p > i) {
-          const uint64_t a = cand[i], b = cand[p];
-          const bool desc = (i & k) == 0;
-          if (desc ? (a < b) : (a > b)) {
-            cand[i] = b;
-            cand[p] = a;
-          }
-        }
-      }
-      __syncthreads();
+      pmask |= (uint32_t)(nb - 1) << shift;
+      least = prefix;
+      exact = above + scount <= CAP;
     }
   }
-  for (int r = tid; r < K; r += kTK)
-    out[(int64_t)g * K + r] = r < take ? lo + (int)(0xFFFFFFFFu - (uint32_t)(cand[r] & 0xFFFFFFFFull)) : -1;
+  __syncthreads();
+  if (exact) {
+    visit([&](uint32_t k, int i) {
+      if (k >= least) cand[atomicAdd(&cnt, 1)] = code_of(k, i);
+    });
+    __syncthreads();
+  } else {
+    // more keys equal to the K-th than fit: those above it, then the first
+    // krem equal ones in index order
+    int eq_base = 0;
+    for (int t0 = 0; t0 < n; t0 += kTK) {
+      const int i = t0 + tid;
+      const bool ok = i < n;
+      const uint32_t k = ok ? score_key(s[lo + i]) : 0u;
+      if (ok && k > least) cand[atomicAdd(&cnt, 1)] = code_of(k, i);
+      const bool eq = ok && k == least;
+      int all;
+      const int r = block_prefix(eq, wsum, &all);
+      if (eq && eq_base + r < krem) cand[(take - krem) + eq_base + r] = code_of(k, i);
+      eq_base += all;
+    }
+    __syncthreads();
+    if (tid == 0) cnt = take;
+    __syncthreads();
+  }
+  const int m = cnt;
+  for (int i = tid; i < m; i += kTK) {
+    const uint64_t mine = cand[i];
+    int rank = 0, q = 0;
+#pragma unroll 4
+    for (; q + 1 < m; q += 2) {
+      const ulonglong2 v = *reinterpret_cast<const ulonglong2*>(&cand[q]);
+      rank += (v.x > mine) + (v.y > mine);
+    }
+    if (q < m) rank += cand[q] > mine;
+    if (rank < take) out[(int64_t)g * K + rank] = lo + (int)(0xFFFFFFFFu - (uint32_t)(mine & 0xFFFFFFFFull));
+  }
+  for (int r = take + tid; r < K; r += kTK) out[(int64_t)g * K + r] = -1;
 }
 
 // ---------------------------------------------------------------- RDU selection
@@ -850,9 +894,9 @@ hipError_t launch_topk_score(int n_seg, const int* offs, const float* s, const f
 hipError_t launch_topk(int n_seg, const int* offs, const float* s, int K, int* out, hipStream_t st) {
   if (n_seg <= 0 || K < 1 || K > 1024) return hipErrorInvalidValue;
 #define TCL_TOPK(PP) hipLaunchKernelGGL((topk_kernel<PP>), dim3(n_seg), dim3(kTK), 0, st, offs, s, K, out)
-  if (K <= 64) TCL_TOPK(64);
-  else if (K <= 256) TCL_TOPK(256);
-  else TCL_TOPK(1024);
+  if (K <= 64) TCL_TOPK(256);
+  else if (K <= 256) TCL_TOPK(512);
+  else TCL_TOPK(1536);
 #undef TCL_TOPK
   return hipGetLastError();
 }
