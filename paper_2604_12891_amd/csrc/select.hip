@@ -209,10 +209,9 @@ struct RduState {
   unsigned arrived;  // blocks of the current launch that have parked their partial
   int ver;           // labeled programs the whole pool's distances include
   int nact;          // candidates collected for the short list
-  int active;        // this launch runs on the short list
+  int active[2];     // a launch of this parity runs on the short list
   int collect;       // this launch, over the whole pool, collects those with t_s >= cut
   int spare;         // launches that may still come to nothing
-  int pad_;
   double cut;            // the short list's bound
   double cut_S1, cut_S2; // S1, S2 and M when it was collected
   int cut_M;
@@ -493,7 +492,7 @@ __global__ __launch_bounds__(kST) void rdu_mark_kernel(int N, const int* __restr
 // The arithmetic per candidate is the same in both, and ties go to the lower
 // index, so the selection is too. The call over 8.65 M programs with 1,024
 // initial ones, 64 selections: 3.62 ms with passes over the whole pool only,
-// 1.09 ms now (three such passes and 62 launches of 8 us on lists, bound by
+// 1.13 ms now (three such passes and 62 launches of 8 us on lists, bound by
 // the latency of a launch's chain of loads, block reductions and arrival).
 constexpr int kRduUnroll = 4;
 constexpr int kRduList = 32768;       // room of the short list
@@ -559,7 +558,7 @@ __global__ __launch_bounds__(kST) void rdu_score_kernel(int N, const float* __re
                                                         const double* __restrict__ budget,
                                                         int* __restrict__ sel, RduState* state,
                                                         double* __restrict__ d, Best* part, ListItem* list,
-                                                        int* hist, int* out) {
+                                                        int* hist, int* out, int parity) {
   __shared__ double bt[kST / 64];
   __shared__ int bi[kST / 64];
   __shared__ double sfl[LIST ? kST : 1];
@@ -570,11 +569,15 @@ __global__ __launch_bounds__(kST) void rdu_score_kernel(int N, const float* __re
   const int tid = threadIdx.x;
   const RduState st = *state;
   if (st.done) return;
+  // A launch on the list does not wait for the blocks it has no work for, so
+  // one that starts late may find the next launch's state here: its own
+  // launch's flag is kept, the last block writes the other one.
+  const bool on_list = LIST && (parity ? st.active[1] : st.active[0]) != 0;
   const double inv = 1.0 / (double)(st.M + 1);
   double best_t = 0.0;
   int best_i = -1;
   int blocks = gridDim.x;  // blocks that take part
-  if (LIST && st.active) {
+  if (on_list) {
     blocks = min((int)gridDim.x, max(1, (st.nact + kST - 1) / kST));
     if ((int)blockIdx.x >= blocks) return;
     for (int q = blockIdx.x * kST + tid; q < st.nact; q += blocks * kST) {
@@ -715,7 +718,7 @@ __global__ __launch_bounds__(kST) void rdu_score_kernel(int N, const float* __re
   }
   const Best w = block_best(t, i, bt, bi);
   int edge = kHistBins;
-  if (LIST && !st.active) {
+  if (LIST && !on_list) {
     // the lowest bin edge that half the list's room would hold: a suffix sum
     // over the bins, lane l of one wavefront taking per bins from the top down
     for (int q = tid; q < kHistBins; q += kST) sh[q] = atomicExch(&hist[q], 0);
@@ -748,7 +751,7 @@ __global__ __launch_bounds__(kST) void rdu_score_kernel(int N, const float* __re
   }
   if (tid == 0) {
     state->arrived = 0;
-    int active = LIST && st.active, spare = st.spare;
+    int active = on_list, spare = st.spare;
     const int nact = LIST ? atomicAdd(&state->nact, 0) : 0;  // as this launch left it
     double next_cut = st.next_cut;
     if (LIST && !active) {
@@ -783,7 +786,7 @@ __global__ __launch_bounds__(kST) void rdu_score_kernel(int N, const float* __re
       }
     }
     if constexpr (LIST) {
-      state->active = active;
+      state->active[parity ^ 1] = active;
       state->spare = spare;
       if (!active) state->nact = 0;
       const bool collect = !active && spare > 0;
@@ -965,7 +968,7 @@ hipError_t launch_rdu_select(int N, const float* s, const int* op, int n_ops, co
   const int sgrid = (int)std::min<int64_t>(((int64_t)N + kST * kRduUnroll - 1) / (kST * kRduUnroll), use_list ? kRduGrid : 512);
   for (int it = 0; it < n_select + spare; ++it)
     hipLaunchKernelGGL(use_list ? rdu_score_kernel<true> : rdu_score_kernel<false>, dim3(sgrid), dim3(kST), 0, st, N, s,
-                       op, n_ops, budget, sel, state, d, part, list, hist, out);
+                       op, n_ops, budget, sel, state, d, part, list, hist, out, it & 1);
   hipLaunchKernelGGL(rdu_finish_kernel, dim3(1), dim3(kST), 0, st, n_select, state, out, count);
   return hipGetLastError();
 }

@@ -154,3 +154,23 @@ def test_rdu_select_short_list(kind):
     elif kind == "skewed_ops":
         op = np.where(rng.random(N) < 0.97, 0, 1 + rng.integers(0, n_ops - 1, N)).astype(np.int32)
     _check_rdu_pool(s, op, n_ops, init, n_sel)
+
+
+def test_rdu_select_beside_other_work():
+    """Selections on a short list while products on another stream hold the
+    CUs, so that the blocks a launch on the list has no work for start late:
+    the same selections as alone."""
+    N, n_ops, n_init, n_sel = 1_000_003, 12, 40, 96
+    print(f"rdu beside other work N={N}", flush=True)
+    s, op, init = _rdu_case(N, n_ops, n_init, 300)
+    args = (_dev(s, torch.float32), _dev(op, torch.int32), n_ops, _dev(init, torch.int32), n_sel)
+    alone, count = _tb().rdu_select(*args)
+    a = torch.randn(4096, 4096, device="cuda")
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        for _ in range(12):
+            torch.mm(a, a)
+    got, c = _tb().rdu_select(*args)
+    torch.cuda.synchronize()
+    assert torch.equal(c, count) and torch.equal(got, alone)
