@@ -45,6 +45,27 @@ def test_topk_matches_oracle(sizes, K):
     assert np.array_equal(got.cpu().numpy(), ref)
 
 
+@pytest.mark.parametrize("K", [64, 65, 256, 1024])
+@pytest.mark.parametrize("kind", ["random", "equal", "close", "nan"])
+def test_topk_radix_edges(kind, K):
+    """Segments around K and around the 8,192 keys that stay in registers;
+    scores all equal, or closer than the first digits tell apart (more
+    candidates than fit, so further digits and the index order decide), or
+    NaN but for a few."""
+    sizes = [K - 1, K, K + 1, 8191, 8192, 8193, 16385]
+    print(f"topk edges {kind} K={K}", flush=True)
+    rng = np.random.default_rng(K)
+    offs = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    n = int(offs[-1])
+    s = {"random": lambda: 0.3 * rng.standard_normal(n),
+         "equal": lambda: np.full(n, -0.5),
+         "close": lambda: 1.0 + rng.integers(0, 40, n) * 2.0 ** -23,
+         "nan": lambda: np.where(rng.random(n) < 0.002, rng.standard_normal(n), np.nan)}[kind]().astype(np.float32)
+    got = _tb().topk(_dev(s, torch.float32), _dev(offs, torch.int32), K)
+    torch.cuda.synchronize()
+    assert np.array_equal(got.cpu().numpy(), osel.topk_segments(s, offs, K))
+
+
 def test_topk_of_a_scored_round():
     """The top 64 of the headline tuning round's scores as the model would
     produce them (seeded score-like values, one segment per 512 candidates)."""
