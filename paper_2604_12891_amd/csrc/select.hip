@@ -16,6 +16,8 @@
 // time when they come up as the argmax, which leaves the same sequence of
 // labeled programs. fp64 throughout (the normalised predictions, distances,
 // sums and t_s).
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -209,14 +211,22 @@ struct RduState {
   unsigned arrived;  // blocks of the current launch that have parked their partial
   int ver;           // labeled programs the whole pool's distances include
   int nact;          // candidates collected for the short list
-  int active[2];     // a launch of this parity runs on the short list
+  int mode[2];       // what a launch of this parity does: RduMode
   int collect;       // this launch, over the whole pool, collects those with t_s >= cut
   int spare;         // launches that may still come to nothing
   double cut;            // the short list's bound
   double cut_S1, cut_S2; // S1, S2 and M when it was collected
   int cut_M;
   int run;               // selections made from it
+  int balance, cost;     // selections that lists served, less the cost of each try at one
+  int wait, back, back0; // kRduPlain launches until the next try, and how many the time after
   double next_cut;       // the bound the last pass over the whole pool suggests
+};
+
+enum RduMode {
+  kRduWhole,  // over the whole pool, with every label since the last such launch; may sample and collect
+  kRduListed, // over the short list
+  kRduPlain,  // over the whole pool, with the last label
 };
 
 struct Best {
@@ -358,6 +368,13 @@ __global__ __launch_bounds__(kST) void rdu_setup_kernel(int N, const float* __re
     st.n_select = n_select;
     st.done = (n_select <= 0 || rc[0] == 0) ? 1 : 0;
     st.spare = spare;
+    // measured over 140,000 to 8.65 M programs, 8 to 512 selections of equal,
+    // tied, log-normal, normal and sorted scores: half of this cost is within 2 %,
+    // twice as much loses up to 9 %, four times up to half; without a wait 2.6
+    // times the call (64 different scores, 8.65 M, 512 selections), waiting for
+    // good 2.3 times (normal scores there)
+    st.balance = st.cost = N < 524288 ? 4 : 1;
+    st.back = st.back0 = N < 524288 ? 32 : 8;
     *state = st;
   }
 }
@@ -485,10 +502,19 @@ __global__ __launch_bounds__(kST) void rdu_mark_kernel(int N, const int* __restr
 // cut, and the next launches run on that short list alone: while the list's
 // best is at or above cut plus the rise since, no candidate outside it can
 // win. When it no longer is, the launch selects nothing and the next one
-// takes the whole pool again (at most `spare` times, then all of them do, so
-// that n_select + spare launches always suffice). The cut comes from a
-// histogram of a sample of t_s, for half the list's room; a list that
-// overflows is not used.
+// takes the whole pool again (at most `spare` times, so that n_select + spare
+// launches always suffice). The cut comes from a histogram of a sample of t_s,
+// for half the list's room; a list that overflows is not used.
+// Scores that many candidates share, or that have a few far outliers, give
+// lists that are empty, overflow or serve few selections. So lists are kept
+// an account: the selections they served less `cost` for each try. When it is
+// overdrawn, `wait` launches neither sample nor collect (kRduPlain, the pass
+// that pools without the list get) before the next try, twice as many each time until a
+// list serves more than its cost. The call over 140,000 / 1 M / 8.65 M programs,
+// 64 selections, us: equal scores 1,605 / 2,713 / 4,425 without the account, 741 /
+// 1,376 / 2,869 with it (722 / 1,908 / 3,545 with passes over the whole pool only,
+// of 1,024 blocks); 64 different scores 1,306 / 2,913 / 3,789, 790 / 1,504 / 3,336
+// (759 / 1,958 / 3,625).
 // The arithmetic per candidate is the same in both, and ties go to the lower
 // index, so the selection is too. The call over 8.65 M programs with 1,024
 // initial ones, 64 selections: 3.62 ms with passes over the whole pool only,
@@ -497,6 +523,9 @@ __global__ __launch_bounds__(kST) void rdu_mark_kernel(int N, const int* __restr
 constexpr int kRduUnroll = 4;
 constexpr int kRduList = 32768;       // room of the short list
 constexpr double kRiseMargin = 1e-12;  // far above the rounding of u_s and of its change (a few 1e-16)
+
+constexpr int kRduPlainGrid = 512;     // blocks of a kRduPlain launch
+constexpr int kRduMaxBalance = 256;    // selections that lists may be behind after a long good stretch
 
 constexpr int kRduHeld = 256 + kST * kRduUnroll;  // of them held in LDS by a block: 256 and a round's
 
@@ -565,41 +594,27 @@ __global__ __launch_bounds__(kST) void rdu_score_kernel(int N, const float* __re
   __shared__ int sil[LIST ? kST : 1];
   __shared__ int sh[LIST ? kHistBins : 1];
   __shared__ ListItem held[LIST ? kRduHeld : 1];
-  __shared__ int nheld, flag;
-  const int tid = threadIdx.x;
+  __shared__ int nheld, flag, above;
+  const int tid = threadIdx.x, lane = tid & 63;
   const RduState st = *state;
   if (st.done) return;
-  // A launch on the list does not wait for the blocks it has no work for, so
-  // one that starts late may find the next launch's state here: its own
-  // launch's flag is kept, the last block writes the other one.
-  const bool on_list = LIST && (parity ? st.active[1] : st.active[0]) != 0;
+  // A launch does not wait for the blocks that it has no work for (on the list,
+  // and kRduPlain's past its grid), so one that starts late may find the next
+  // launch's state here: its own launch's mode is kept, the last block writes
+  // the other one.
+  const int mode = LIST ? (parity ? st.mode[1] : st.mode[0]) : (int)kRduPlain;
   const double inv = 1.0 / (double)(st.M + 1);
   double best_t = 0.0;
   int best_i = -1;
   int blocks = gridDim.x;  // blocks that take part
-  if (on_list) {
-    blocks = min((int)gridDim.x, max(1, (st.nact + kST - 1) / kST));
-    if ((int)blockIdx.x >= blocks) return;
-    for (int q = blockIdx.x * kST + tid; q < st.nact; q += blocks * kST) {
-      ListItem it = list[q];
-      const double dn = it.i == st.last ? -1.0 : fabs(it.f - fhat(s, st.last, st));
-      if (it.d >= 0.0) {
-        if ((double)sel[it.op] >= budget[it.op]) it.d = -1.0;
-        else it.d = fmin(it.d, dn);
-        list[q].d = it.d;
-      }
-      const double t = rdu_t(it.f, it.d, st, inv);
-      if (it.d >= 0.0 && better(t, it.i, best_t, best_i)) {
-        best_t = t;
-        best_i = it.i;
-      }
-    }
-  } else {
-    // the labels this pass brings into the distances: those since the last
-    // one, the first kST of them from LDS (without the list, the last label)
-    const int np = LIST ? st.count - st.ver : min(st.count, 1), npl = min(np, kST);
-    const double last_f = !LIST && np ? fhat(s, st.last, st) : 0.0;
-    if constexpr (LIST) {
+  // one pass over the whole pool: FULL with every label since the last one
+  // (the first kST of them from LDS), sampling and collecting; else with the
+  // last label
+  auto pool = [&](auto FULL) {
+    constexpr bool kFull = decltype(FULL)::value;
+    const int np = kFull ? st.count - st.ver : min(st.count, 1), npl = min(np, kST);
+    const double last_f = !kFull && np ? fhat(s, st.last, st) : 0.0;
+    if constexpr (kFull) {
       for (int b = tid; b < kHistBins; b += kST) sh[b] = 0;
       if (tid < npl) {
         sil[tid] = out[st.ver + tid];
@@ -609,21 +624,23 @@ __global__ __launch_bounds__(kST) void rdu_score_kernel(int N, const float* __re
       __syncthreads();
     }
     const double base = u_min(st.S1, st.S2, inv);
-    const bool sampled = (blockIdx.x & (kHistEvery / 4 - 1)) == 0;
-    // the block's held items to the list (as far as it has room; the count
-    // goes on, so an overfull list is noticed)
+    const bool sampled = kFull && st.spare > 0 && st.wait == 0 && (blockIdx.x & (kHistEvery / 4 - 1)) == 0;
+    bool collect = kFull && st.collect;  // block-uniform
+    // the block's held items to the list, as far as it has room (the count
+    // goes on, so an overfull list is noticed, and this block stops collecting)
     auto append = [&](int n) {
       if (tid == 0 && n) flag = atomicAdd(&state->nact, n);
       __syncthreads();
       for (int q = tid; q < n; q += kST)
         if (flag + q < kRduList) list[flag + q] = held[q];
+      if (n && flag + n > kRduList) collect = false;
       __syncthreads();
       if (tid == 0) nheld = 0;
       __syncthreads();
     };
     constexpr int U = kRduUnroll;
     static_assert(U == 4, "the sample takes one of a round's four");
-    for (int64_t j0 = (int64_t)blockIdx.x * kST * U; j0 < N; j0 += (int64_t)gridDim.x * kST * U) {
+    for (int64_t j0 = (int64_t)blockIdx.x * kST * U; j0 < N; j0 += (int64_t)blocks * kST * U) {
       // every load at a clamped place and without a condition, so that a
       // round's twelve, then its eight lookups by type, are in flight together
       double dv[U], fv[U], bud[U];
@@ -649,8 +666,8 @@ __global__ __launch_bounds__(kST) void rdu_score_kernel(int N, const float* __re
         low[k] = false;
       }
       for (int p = 0; p < np; ++p) {
-        const int il = !LIST ? st.last : p < npl ? sil[p] : out[st.ver + p];
-        const double fl = !LIST ? last_f : p < npl ? sfl[p] : fhat(s, il, st);
+        const int il = !kFull ? st.last : p < npl ? sil[p] : out[st.ver + p];
+        const double fl = !kFull ? last_f : p < npl ? sfl[p] : fhat(s, il, st);
 #pragma unroll
         for (int k = 0; k < U; ++k) {
           const double dn = il == iv[k] ? -1.0 : fabs(fv[k] - fl);  // a labeled program is no candidate
@@ -675,26 +692,71 @@ __global__ __launch_bounds__(kST) void rdu_score_kernel(int N, const float* __re
           best_t = t;
           best_i = i;
         }
-        if constexpr (LIST) {
-          if (k == 0 && sampled && cand) atomicAdd(&sh[hist_bin(t - base)], 1);
-          if (st.collect && cand && t >= st.cut)
-            held[atomicAdd(&nheld, 1)] = ListItem{fv[k], dv[k], i, o};
+        if constexpr (kFull) {
+          // one atomic for the lanes that share the first one's bin, and one
+          // for a wavefront's collected candidates: with equal scores 64 lanes
+          // would queue at one address
+          const uint64_t cands = __builtin_amdgcn_ballot_w64(cand);
+          if (k == 0 && sampled && cands) {
+            const int bin = cand ? hist_bin(t - base) : -1;
+            const int first = __builtin_amdgcn_readlane(bin, __builtin_ctzll(cands));
+            const uint64_t same = __builtin_amdgcn_ballot_w64(bin == first);
+            if (bin == first) {
+              if (lane == __builtin_ctzll(same)) atomicAdd(&sh[first], __builtin_popcountll(same));
+            } else if (cand) {
+              atomicAdd(&sh[bin], 1);
+            }
+          }
+          const bool take = collect && cand && t >= st.cut;
+          const uint64_t takes = __builtin_amdgcn_ballot_w64(take);
+          if (takes) {
+            const int first = __builtin_ctzll(takes);
+            int at = 0;
+            if (lane == first) at = atomicAdd(&nheld, __builtin_popcountll(takes));
+            at = __builtin_amdgcn_readlane(at, first);
+            if (take)
+              held[at + __builtin_popcountll(takes & ((1ull << lane) - 1))] = ListItem{fv[k], dv[k], i, o};
+          }
         }
       }
-      if (LIST && st.collect) {  // block-uniform
+      if (kFull && collect) {
         __syncthreads();
         const int n = nheld;
         if (n > kRduHeld - kST * kRduUnroll) append(n);
         else __syncthreads();  // nheld is read before the next round adds to it
       }
     }
-    if constexpr (LIST) {
+    if constexpr (kFull) {
       __syncthreads();
-      if (st.collect) append(nheld);
+      if (collect) append(nheld);
       if (sampled)
         for (int b = tid; b < kHistBins; b += kST)
           if (sh[b]) atomicAdd(&hist[b], sh[b]);
     }
+  };
+  if (mode == kRduListed) {
+    blocks = min((int)gridDim.x, max(1, (st.nact + kST - 1) / kST));
+    if ((int)blockIdx.x >= blocks) return;
+    for (int q = blockIdx.x * kST + tid; q < st.nact; q += blocks * kST) {
+      ListItem it = list[q];
+      const double dn = it.i == st.last ? -1.0 : fabs(it.f - fhat(s, st.last, st));
+      if (it.d >= 0.0) {
+        if ((double)sel[it.op] >= budget[it.op]) it.d = -1.0;
+        else it.d = fmin(it.d, dn);
+        list[q].d = it.d;
+      }
+      const double t = rdu_t(it.f, it.d, st, inv);
+      if (it.d >= 0.0 && better(t, it.i, best_t, best_i)) {
+        best_t = t;
+        best_i = it.i;
+      }
+    }
+  } else if (LIST && mode == kRduWhole) {
+    if constexpr (LIST) pool(std::true_type{});
+  } else {
+    blocks = min((int)gridDim.x, kRduPlainGrid);
+    if ((int)blockIdx.x >= blocks) return;
+    pool(std::false_type{});
   }
   const Best b = block_best(best_t, best_i, bt, bi);
   if (tid == 0) {
@@ -718,22 +780,26 @@ __global__ __launch_bounds__(kST) void rdu_score_kernel(int N, const float* __re
   }
   const Best w = block_best(t, i, bt, bi);
   int edge = kHistBins;
-  if (LIST && !on_list) {
+  const bool sampling = LIST && mode == kRduWhole && st.spare > 0 && st.wait == 0;
+  if (sampling) {
     // the lowest bin edge that half the list's room would hold: a suffix sum
     // over the bins, lane l of one wavefront taking per bins from the top down
     for (int q = tid; q < kHistBins; q += kST) sh[q] = atomicExch(&hist[q], 0);
-    if (tid == 0) flag = kHistBins;
+    if (tid == 0) {
+      flag = kHistBins;
+      above = 0;
+    }
     __syncthreads();
+    constexpr int per = (kHistBins + 63) / 64;
+    int own[per], sum = 0, before = 0;
     if (tid < 64) {
-      constexpr int per = (kHistBins + 63) / 64;
-      int own[per], sum = 0;
 #pragma unroll
       for (int r = 0; r < per; ++r) {
         const int q = kHistBins - 1 - (tid * per + r);
         sum += q >= 0 ? sh[q] : 0;
         own[r] = sum;
       }
-      int before = sum;
+      before = sum;
 #pragma unroll
       for (int o = 1; o < 64; o <<= 1) {
         const int v = __shfl_up(before, o, 64);
@@ -748,22 +814,35 @@ __global__ __launch_bounds__(kST) void rdu_score_kernel(int N, const float* __re
     }
     __syncthreads();
     edge = flag;
+    if (tid < 64) {
+#pragma unroll
+      for (int r = 0; r < per; ++r)
+        if (kHistBins - 1 - (tid * per + r) == edge) above = before + own[r];
+    }
+    __syncthreads();
   }
   if (tid == 0) {
     state->arrived = 0;
-    int active = on_list, spare = st.spare;
-    const int nact = LIST ? atomicAdd(&state->nact, 0) : 0;  // as this launch left it
+    bool active = mode == kRduListed, collect = false;
+    int spare = st.spare, balance = st.balance, wait = st.wait, next = kRduWhole;
+    const int nact = LIST && st.collect ? atomicAdd(&state->nact, 0) : 0;  // as this launch left it
     double next_cut = st.next_cut;
-    if (LIST && !active) {
-      state->ver = st.count;
+    if (LIST && !active) state->ver = st.count;  // every label but this launch's is in the distances
+    if (sampling) {
       state->next_cut = next_cut = u_min(st.S1, st.S2, inv) + hist_edge(min(edge, kHistBins - 1));
+      collect = above > 0;  // no cut that a list could be collected with otherwise
     }
+    // the list that this launch collected, if it is of use
+    const bool listed = mode == kRduWhole && st.collect && nact >= 2 && nact <= kRduList;
+    if (sampling && !listed && (!collect || st.collect)) balance -= st.cost;
+    if (mode == kRduPlain && wait > 0) --wait;
     if (active && (w.i < 0 || !(w.t >= st.cut + u_rise(st)))) {
       // a candidate outside the list may be better: the whole pool next
-      // (a list that served a single selection was not worth its launch: that
-      // counts four times)
-      spare = max(0, spare - (st.run < 2 ? 4 : 1));
-      active = 0;
+      balance = min(balance + st.run - st.cost, kRduMaxBalance);
+      if (st.run > st.cost) state->back = st.back0;
+      --spare;
+      active = false;
+      collect = true;
     } else if (w.i < 0) {
       state->done = 1;
     } else {
@@ -777,8 +856,8 @@ __global__ __launch_bounds__(kST) void rdu_score_kernel(int N, const float* __re
       sel[op[w.i]] += 1;
       if (st.count + 1 >= st.n_select) state->done = 1;
       state->run = st.run + 1;
-      if (LIST && st.collect && nact <= kRduList) {
-        active = 1;  // the list just collected holds every t_s >= cut
+      if (listed) {
+        active = true;  // it holds every t_s >= cut
         state->cut_S1 = st.S1;
         state->cut_S2 = st.S2;
         state->cut_M = st.M;
@@ -786,10 +865,19 @@ __global__ __launch_bounds__(kST) void rdu_score_kernel(int N, const float* __re
       }
     }
     if constexpr (LIST) {
-      state->active[parity ^ 1] = active;
+      if (balance < 0) {
+        balance = 0;
+        wait = st.back;
+        state->back = min(2 * st.back, 1 << 20);
+      }
+      // distances without the labels of a list's run need kRduWhole
+      if (mode != kRduListed && (wait > 0 || spare == 0)) next = kRduPlain;
+      collect = collect && !active && next == kRduWhole && wait == 0 && spare > 0;
+      state->mode[parity ^ 1] = active ? (int)kRduListed : next;
       state->spare = spare;
+      state->balance = balance;
+      state->wait = wait;
       if (!active) state->nact = 0;
-      const bool collect = !active && spare > 0;
       state->collect = collect;
       if (collect) state->cut = next_cut;
     }
@@ -965,7 +1053,8 @@ hipError_t launch_rdu_select(int N, const float* s, const int* op, int n_ops, co
   // pass with 512 blocks, 53.0 with 768, 57.1 with 1,024; 1 M 19.6, 24.5, 28.3.
   // With the list, whose few passes collect too: 1.19 ms a call with 512, 1.10
   // with 1,024
-  const int sgrid = (int)std::min<int64_t>(((int64_t)N + kST * kRduUnroll - 1) / (kST * kRduUnroll), use_list ? kRduGrid : 512);
+  const int sgrid = (int)std::min<int64_t>(((int64_t)N + kST * kRduUnroll - 1) / (kST * kRduUnroll),
+                                           use_list ? kRduGrid : kRduPlainGrid);
   for (int it = 0; it < n_select + spare; ++it)
     hipLaunchKernelGGL(use_list ? rdu_score_kernel<true> : rdu_score_kernel<false>, dim3(sgrid), dim3(kST), 0, st, N, s,
                        op, n_ops, budget, sel, state, d, part, list, hist, out, it & 1);

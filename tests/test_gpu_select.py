@@ -195,3 +195,35 @@ def test_rdu_select_beside_other_work():
     got, c = _tb().rdu_select(*args)
     torch.cuda.synchronize()
     assert torch.equal(c, count) and torch.equal(got, alone)
+
+
+def _least_us(f, calls=3, rounds=7):
+    """The least time of a call, over rounds of a few calls each."""
+    f()
+    torch.cuda.synchronize()
+    best = float("inf")
+    for _ in range(rounds):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(calls):
+            f()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) / calls * 1e3)
+    return best
+
+
+@pytest.mark.parametrize("kind", ["constant", "coarse"])
+def test_rdu_select_pools_that_defeat_the_list(kind):
+    """Equal scores, and 64 different ones, give short lists that are empty or
+    overflow: the call costs what it costs with too few initial programs for
+    the list (24: passes over the whole pool only), not a multiple (it was
+    2.0 and 2.2 times, and is within 10 %)."""
+    N, n_ops, n_sel = 1_000_003, 20, 64
+    print(f"rdu without a list {kind}", flush=True)
+    s, op, init = _rdu_case(N, n_ops, 1024, 400)
+    s = np.full(N, 0.25, np.float32) if kind == "constant" else (np.round(s * 16) / 16).astype(np.float32)
+    s, op, init = _dev(s, torch.float32), _dev(op, torch.int32), _dev(init, torch.int32)
+    ws = torch.empty(_tb().lib().tcl_rdu_workspace_bytes(N, n_ops), dtype=torch.uint8, device="cuda")
+    us = [_least_us(lambda i=i: _tb().rdu_select(s, op, n_ops, i, n_sel, workspace=ws)) for i in (init, init[:24])]
+    assert us[0] < 1.4 * us[1], us
