@@ -436,10 +436,14 @@ TCL_API tcl_status tcl_topk_score(int32_t n_seg, const int32_t* d_seg_offsets, c
  *   toward neither n_select nor the budgets;
  *   d_selected [n_select] int32 output, in selection order, -1 past the end;
  *   d_count [1] int32 output, the number selected;
- *   d_workspace >= tcl_rdu_workspace_bytes(N, n_ops) bytes, 256-byte aligned.
+ *   d_workspace: tcl_rdu_workspace_bytes(N, n_ops) bytes, 256-byte aligned.
+ *   Above 131,072 programs 0.8 MB of them are for a list of the best
+ *   candidates; without that room the call makes the same selections by
+ *   passes over the whole pool.
  * Scores must be finite (a NaN-scored program is never selected, and must
- * not be in d_initial). fp64 arithmetic on the device; the host enqueues two
- * kernels per selection and never waits. */
+ * not be in d_initial). fp64 arithmetic on the device; the host enqueues one
+ * kernel per selection, with the list n_select / 8 + 4 more that may find
+ * nothing left to do, and never waits. */
 TCL_API size_t tcl_rdu_workspace_bytes(int32_t N, int32_t n_ops);
 TCL_API tcl_status tcl_rdu_select(int32_t N, const float* d_scores, const int32_t* d_op, int32_t n_ops,
                                   const int32_t* d_initial, int32_t n_initial, int32_t n_select,

@@ -425,13 +425,17 @@ def rdu_select(scores, op, n_ops, initial, n_select, workspace=None, stream=None
     N = scores.numel()
     sel = torch.empty(max(n_select, 1), dtype=torch.int32, device=scores.device)
     cnt = torch.empty(1, dtype=torch.int32, device=scores.device)
-    need = lib().tcl_rdu_workspace_bytes(N, n_ops)
-    ws = workspace
-    if ws is None or ws.numel() * ws.element_size() < need:
-        ws = torch.empty(max(need, 256), dtype=torch.uint8, device=scores.device)
-    check(lib().tcl_rdu_select(N, scores.data_ptr(), op.data_ptr(), n_ops, initial.data_ptr(), initial.numel(),
-                               n_select, sel.data_ptr(), cnt.data_ptr(), ws.data_ptr(),
-                               ws.numel() * ws.element_size(), _stream(stream)))
+
+    def call(ws):
+        return lib().tcl_rdu_select(N, scores.data_ptr(), op.data_ptr(), n_ops, initial.data_ptr(), initial.numel(),
+                                    n_select, sel.data_ptr(), cnt.data_ptr(), ws.data_ptr(),
+                                    ws.numel() * ws.element_size(), _stream(stream))
+
+    status = -3 if workspace is None else call(workspace)
+    if status == -3:  # TCL_ERR_WORKSPACE: none, or one that is too small
+        need = lib().tcl_rdu_workspace_bytes(N, n_ops)
+        status = call(torch.empty(max(need, 256), dtype=torch.uint8, device=scores.device))
+    check(status)
     return sel[:n_select], cnt
 
 

@@ -974,10 +974,10 @@ TCL_API tcl_status tcl_rdu_select(int32_t N, const float* d_scores, const int32_
   if (!d_scores || !d_op || !d_initial || !d_count || (n_select > 0 && !d_selected) || !d_workspace)
     return fail(TCL_ERR_INVALID_ARG, "NULL device pointer");
   if (reinterpret_cast<uintptr_t>(d_workspace) % 256) return fail(TCL_ERR_INVALID_ARG, "d_workspace must be 256-byte aligned");
-  const size_t need = rdu_workspace_bytes(N, n_ops);
+  const size_t need = rdu_workspace_least_bytes(N, n_ops);
   if (ws_bytes < need) return fail(TCL_ERR_WORKSPACE, "workspace has %zu bytes, needs %zu", ws_bytes, need);
   TCL_HIP(launch_rdu_select(N, d_scores, d_op, n_ops, d_initial, n_initial, n_select, d_selected, d_count,
-                            d_workspace, static_cast<hipStream_t>(stream)));
+                            d_workspace, ws_bytes, static_cast<hipStream_t>(stream)));
   return TCL_OK;
 }
 

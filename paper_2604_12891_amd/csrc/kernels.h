@@ -404,9 +404,12 @@ hipError_t launch_topk_score(int n_seg, const int* offs, const float* s, const f
 // of N: out [n_select] in selection order (-1 past the end), count [1].
 // op [N] in [0, n_ops) (others are never selected), n_ops <= 4096;
 // init [n_init] the initial labeled programs (distinct, in [0, N)).
+// The workspace has at least rdu_workspace_least_bytes; with
+// rdu_workspace_bytes large pools get the short list. Same selections.
+size_t rdu_workspace_least_bytes(int N, int n_ops);
 size_t rdu_workspace_bytes(int N, int n_ops);
 hipError_t launch_rdu_select(int N, const float* s, const int* op, int n_ops, const int* init, int n_init,
-                             int n_select, int* out, int* count, void* ws, hipStream_t st);
+                             int n_select, int* out, int* count, void* ws, size_t ws_bytes, hipStream_t st);
 
 // EWC penalty (Eq. (9)): grad += lam F (theta - prev); loss[3] =
 // lam/2 sum F (theta - prev)^2 and loss[0] += loss[3]. part: ewc_part_floats().

@@ -335,7 +335,9 @@ __global__ __launch_bounds__(kST) void rdu_setup_kernel(int N, const float* __re
     budget[o] = (double)n_select * (double)opcount[o] / (double)N;
     sel[o] = 0;
   }
-  for (int o = threadIdx.x; o < kHistBins; o += kST) hist[o] = 0;
+  if (hist) {
+    for (int o = threadIdx.x; o < kHistBins; o += kST) hist[o] = 0;
+  }
   double a1 = 0.0, a2 = 0.0;
   int c = 0;
   for (int j = threadIdx.x; j < n_init; j += kST) {
@@ -992,17 +994,24 @@ hipError_t launch_topk(int n_seg, const int* offs, const float* s, int K, int* o
   return hipGetLastError();
 }
 
-size_t rdu_workspace_bytes(int N, int n_ops) {
+size_t rdu_workspace_least_bytes(int N, int n_ops) {
   const int grid = std::min((N + kST - 1) / kST, kRduGrid);
   return al256(sizeof(RduState)) + al256((size_t)N * 8) + al256((size_t)n_ops * 8) +
          al256((size_t)(n_ops + 1) * 4) * 2 + al256((size_t)grid * 2 * 4) + al256((size_t)grid * sizeof(Best)) +
-         al256((size_t)kRduList * sizeof(ListItem)) + al256((size_t)kHistBins * 4) +
          al256((size_t)kSortInit * 8) + 256;
 }
 
+// the short list and its histogram, for pools that may use them
+constexpr int kRduListMinN = 4 * kRduList + 1;
+size_t rdu_workspace_bytes(int N, int n_ops) {
+  return rdu_workspace_least_bytes(N, n_ops) +
+         (N >= kRduListMinN ? al256((size_t)kRduList * sizeof(ListItem)) + al256((size_t)kHistBins * 4) : 0);
+}
+
 hipError_t launch_rdu_select(int N, const float* s, const int* op, int n_ops, const int* init, int n_init,
-                             int n_select, int* out, int* count, void* ws, hipStream_t st) {
+                             int n_select, int* out, int* count, void* ws, size_t ws_bytes, hipStream_t st) {
   if (N <= 0 || n_ops <= 0 || n_ops > kMaxOps || n_init < 0 || n_select < 0) return hipErrorInvalidValue;
+  if (ws_bytes < rdu_workspace_least_bytes(N, n_ops)) return hipErrorInvalidValue;
   const int grid = std::min((N + kST - 1) / kST, kRduGrid);
   char* p = static_cast<char*>(ws);
   RduState* state = reinterpret_cast<RduState*>(p);
@@ -1019,13 +1028,10 @@ hipError_t launch_rdu_select(int N, const float* s, const int* op, int n_ops, co
   p += al256((size_t)grid * 2 * 4);
   Best* part = reinterpret_cast<Best*>(p);
   p += al256((size_t)grid * sizeof(Best));
-  ListItem* list = reinterpret_cast<ListItem*>(p);
-  p += al256((size_t)kRduList * sizeof(ListItem));
-  int* hist = reinterpret_cast<int*>(p);
-  p += al256((size_t)kHistBins * 4);
   double* sorted = reinterpret_cast<double*>(p);
   p += al256((size_t)kSortInit * 8);
   int* n_valid = reinterpret_cast<int*>(p);
+  p += 256;
 
   hipLaunchKernelGGL(rdu_zero_kernel, dim3(std::max(1, std::min((n_ops + kST) / kST, 64))), dim3(kST), 0, st,
                      n_ops + 1, opcount);
@@ -1036,7 +1042,16 @@ hipError_t launch_rdu_select(int N, const float* s, const int* op, int n_ops, co
   // programs with 1,024, 256, 128 and 64 initial ones 17 / 57, 40 / 57, 61 / 57
   // and 63 / 57, 1 M with 64 and 32 13.6 / 28 and 24 / 28, 262,000 with 32 10.9 /
   // 13.1, 100,000 with 64 9.6 / 9.6, 40,000 with 64 9.3 / 8.5.
-  const bool use_list = N > 4 * kRduList && n_init >= 32 && (int64_t)n_init * 40000 >= N;
+  // A workspace without room for it is served as it always was, by plain passes.
+  const bool use_list = N >= kRduListMinN && n_init >= 32 && (int64_t)n_init * 40000 >= N &&
+                        ws_bytes >= rdu_workspace_bytes(N, n_ops);
+  ListItem* list = nullptr;
+  int* hist = nullptr;
+  if (use_list) {
+    list = reinterpret_cast<ListItem*>(p);
+    p += al256((size_t)kRduList * sizeof(ListItem));
+    hist = reinterpret_cast<int*>(p);
+  }
   // launches beyond n_select that may select nothing
   const int spare = use_list ? n_select / 8 + 4 : 0;
   hipLaunchKernelGGL(rdu_setup_kernel, dim3(1), dim3(kST), 0, st, N, s, n_ops, init, n_init, n_select, mm, grid,

@@ -227,3 +227,50 @@ def test_rdu_select_pools_that_defeat_the_list(kind):
     ws = torch.empty(_tb().lib().tcl_rdu_workspace_bytes(N, n_ops), dtype=torch.uint8, device="cuda")
     us = [_least_us(lambda i=i: _tb().rdu_select(s, op, n_ops, i, n_sel, workspace=ws)) for i in (init, init[:24])]
     assert us[0] < 1.4 * us[1], us
+
+
+def _rdu_bytes_without_list(N, n_ops):
+    def up(b):
+        return (b + 255) // 256 * 256
+    grid = min((N + 255) // 256, 1024)
+    return 256 + up(8 * N) + up(8 * n_ops) + 2 * up(4 * (n_ops + 1)) + up(8 * grid) + up(16 * grid) + up(8 * 8192) + 256
+
+
+@pytest.mark.parametrize("N", [200_003, 600_001])
+@pytest.mark.parametrize("kind", ["normal", "coarse", "ties", "constant", "lognormal", "sorted", "budgets", "nan"])
+def test_rdu_select_without_room_for_the_list(N, kind):
+    """A workspace of the size that large pools needed before they had the
+    short list is accepted, nothing past its end is written, and the
+    selections are those with the list: 200 of them, so that lists come to
+    little, are waited for and tried again; one byte less is refused."""
+    n_ops, n_init, n_sel = 9, 48, 200
+    print(f"rdu without room {kind} N={N}", flush=True)
+    s, op, init = _rdu_case(N, n_ops, n_init, 500)
+    rng = np.random.default_rng(501)
+    if kind in ("coarse", "ties"):
+        step = 16 if kind == "coarse" else 1000
+        s = (np.round(s * step) / step).astype(np.float32)
+    elif kind == "constant":
+        s[:] = -3.0
+    elif kind == "lognormal":
+        s = np.exp(10 * s).astype(np.float32)
+    elif kind == "sorted":
+        s = np.sort(s)
+    elif kind == "budgets":  # most programs of one type, and types that no program may have
+        op = np.where(rng.random(N) < 0.9, 0, rng.integers(-2, n_ops + 2, N)).astype(np.int32)
+    elif kind == "nan":
+        s[np.setdiff1d(rng.integers(0, N, N // 50), init)] = np.nan
+    s, op, init = _dev(s, torch.float32), _dev(op, torch.int32), _dev(init, torch.int32)
+    tb = _tb()
+    least = _rdu_bytes_without_list(N, n_ops)
+    assert least < tb.lib().tcl_rdu_workspace_bytes(N, n_ops)
+    assert _rdu_bytes_without_list(131_072, n_ops) == tb.lib().tcl_rdu_workspace_bytes(131_072, n_ops)
+    listed, count = tb.rdu_select(s, op, n_ops, init, n_sel)
+    buf = torch.full((least + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    plain, c = tb.rdu_select(s, op, n_ops, init, n_sel, workspace=buf[:least])
+    torch.cuda.synchronize()
+    assert torch.equal(count, c) and torch.equal(listed, plain)
+    assert (buf[least:] == 0x5A).all() and not (buf[:least] == 0x5A).all()
+    st = tb.lib().tcl_rdu_select(N, s.data_ptr(), op.data_ptr(), n_ops, init.data_ptr(), n_init, n_sel,
+                                 plain.data_ptr(), c.data_ptr(), buf.data_ptr(), least - 1, None)
+    assert st == -3  # TCL_ERR_WORKSPACE
