@@ -59,17 +59,22 @@ __device__ __forceinline__ int block_prefix(bool flag, int* wsum, int* total) {
 // first alone when the K-th key's bin is short: with 4,096 scores and K = 64 it
 // holds some 60 keys (an eighth of a power of two), and what lies above and in
 // it fits the candidates. Each candidate's place is then the number of larger
-// ones. Up to kTKeys keys a thread stay in registers. 16 segments of about
-// 4,096, K = 64: 16.7 us with four 8-bit passes over memory and a bitonic sort,
-// 7.3 now: a launch, one round of loads and a dozen barriers. One segment of
-// 65,536, K = 64: 138 -> 27.
+// ones. Up to kTKeys keys a thread stay in registers. Two workgroups fit on a
+// CU (at most 64 VGPRs and 100 SGPRs), for calls of more segments than CUs, and
+// keys that share a bin are counted without 64 lanes queueing for one address.
+// Calls back to back with the scores in cache, K = 64, against four 8-bit passes over
+// memory and a bitonic sort: 16 segments of 4,096 14.3 -> 8.1 us (a launch, one round of
+// loads and a dozen barriers), of equal scores 25.1 -> 14.3; one of 65,536 108 -> 21.
+// 300 segments of 600 with equal scores, K = 10: 14.6 -> 11.0 (19.1 with one workgroup
+// a CU and one atomic a key).
 constexpr int kTKeys = 8;
 template <int CAP>
-__global__ __launch_bounds__(kTK) void topk_kernel(const int* __restrict__ offs, const float* __restrict__ s,
+__global__ __launch_bounds__(kTK, 8) void topk_kernel(const int* __restrict__ offs, const float* __restrict__ s,
                                                    int K, int* __restrict__ out) {
   constexpr int kBins = 4096;
+  static_assert(kBins == 4 * kTK, "four counters a thread");
   __shared__ __attribute__((aligned(16))) uint64_t cand[CAP];
-  __shared__ int hist[kBins];
+  __shared__ __attribute__((aligned(16))) int hist[kBins];
   __shared__ int tot[kTK / 64];
   __shared__ int wsum[kTK / 64];
   __shared__ int sdig, sabove, scount, cnt;
@@ -112,24 +117,34 @@ __global__ __launch_bounds__(kTK) void topk_kernel(const int* __restrict__ offs,
     uint32_t prefix = 0u, pmask = 0u;
     int above = 0;
     exact = false;
-    for (int pass = 0; pass < 3 && !exact; ++pass) {
-      const int shift = pass == 0 ? 20 : pass == 1 ? 10 : 0, nb = pass == 0 ? kBins : 1024;
-      for (int b = tid; b < nb; b += kTK) hist[b] = 0;
+    auto digit = [&](auto PASS) {
+      constexpr int pass = decltype(PASS)::value, shift = pass == 0 ? 20 : pass == 1 ? 10 : 0;
+      reinterpret_cast<int4*>(hist)[tid] = int4{0, 0, 0, 0};
       __syncthreads();
-      visit([&](uint32_t k, int) {
-        if ((k & pmask) == prefix) atomicAdd(&hist[(k >> shift) & (nb - 1)], 1);
+      visit([&](uint32_t k, int i) {
+        if ((k & pmask) != prefix) return;
+        const int bin = pass == 0 ? (int)(k >> 20) : 4 * ((int)(k >> shift) & 1023) + (lane & 3);
+        // close scores share a few bins, where 64 lanes would queue for one
+        // address: a short segment's lanes in the first one's bin count together
+        if (pass == 0 && regs && i < kTK) {
+          const int first = __builtin_amdgcn_readfirstlane(bin);
+          const uint64_t same = __builtin_amdgcn_ballot_w64(bin == first);
+          if (bin != first) atomicAdd(&hist[bin], 1);
+          else if (lane == __builtin_ctzll(same)) atomicAdd(&hist[bin], __builtin_popcountll(same));
+        } else {
+          atomicAdd(&hist[bin], 1);
+        }
       });
       __syncthreads();
-      // thread t takes four digits from nb - 1 - 4 t down; a scan over threads
-      // gives the count of keys at or above each, and exactly one digit has
-      // that count reach krem while the digits above it stay below
-      int c[4], sum = 0;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int d = nb - 1 - (4 * tid + r);
-        c[r] = d >= 0 ? hist[d] : 0;
-        sum += c[r];
-      }
+      // thread t takes four counters from 4095 - 4 t down: four digits, or the
+      // four parts of one, by lane, that the later digits are counted in (one atomic in
+      // four to an address). A scan over threads gives the count of keys at or above
+      // each digit, and exactly one has that count reach krem while the digits
+      // above it stay below
+      const int4 h = reinterpret_cast<const int4*>(hist)[kTK - 1 - tid];
+      const int c[4] = {pass == 0 ? h.w : h.x + h.y + h.z + h.w, pass == 0 ? h.z : 0, pass == 0 ? h.y : 0,
+                        pass == 0 ? h.x : 0};
+      const int sum = c[0] + c[1] + c[2] + c[3];
       int incl = sum;
 #pragma unroll
       for (int o = 1; o < 64; o <<= 1) {
@@ -144,7 +159,7 @@ __global__ __launch_bounds__(kTK) void topk_kernel(const int* __restrict__ offs,
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         if (at < krem && at + c[r] >= krem) {
-          sdig = nb - 1 - (4 * tid + r);
+          sdig = pass == 0 ? kBins - 1 - (4 * tid + r) : kTK - 1 - tid;
           sabove = at;
           scount = c[r];
         }
@@ -154,10 +169,13 @@ __global__ __launch_bounds__(kTK) void topk_kernel(const int* __restrict__ offs,
       krem -= sabove;
       above += sabove;
       prefix |= (uint32_t)sdig << shift;
-      pmask |= (uint32_t)(nb - 1) << shift;
+      pmask |= (pass == 0 ? 0xFFFu : 0x3FFu) << shift;
       least = prefix;
       exact = above + scount <= CAP;
-    }
+    };
+    digit(std::integral_constant<int, 0>{});
+    if (!exact) digit(std::integral_constant<int, 1>{});
+    if (!exact) digit(std::integral_constant<int, 2>{});
   }
   __syncthreads();
   if (exact) {

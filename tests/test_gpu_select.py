@@ -274,3 +274,17 @@ def test_rdu_select_without_room_for_the_list(N, kind):
     st = tb.lib().tcl_rdu_select(N, s.data_ptr(), op.data_ptr(), n_ops, init.data_ptr(), n_init, n_sel,
                                  plain.data_ptr(), c.data_ptr(), buf.data_ptr(), least - 1, None)
     assert st == -3  # TCL_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("kind", ["equal", "close"])
+def test_topk_of_crowded_scores_costs_no_multiple(kind):
+    """More segments than CUs whose scores are equal, or closer than the first
+    digit tells apart: they take at most 1.6 times the time of spread ones (2.0
+    and 1.7 times with one workgroup a CU and one atomic a key)."""
+    n_seg, seg = 300, 600
+    print(f"topk crowded {kind}", flush=True)
+    offs = _dev(np.arange(n_seg + 1) * seg, torch.int32)
+    spread = torch.randn(n_seg * seg, device="cuda")
+    s = torch.full_like(spread, 0.5) if kind == "equal" else 1 + 1e-5 * spread
+    us = [_least_us(lambda x=x: _tb().topk(x, offs, 10), calls=100) for x in (s, spread)]
+    assert us[0] < 1.6 * us[1], us
