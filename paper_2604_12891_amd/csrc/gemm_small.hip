@@ -357,12 +357,16 @@ hipError_t launch_small_acc(const GemmArgs& a, const uint16_t* Wh, int ldwh, hip
 
 }  // namespace
 
-// Measured by padded rows, against the panels: K = 512 18.0 vs 31.7 us at 12,800,
-// 30.9 vs 33.5 at 25,600, 34.7 vs 35.0 at 35,000; K = 256 12.3 vs 18.4 at 10,000;
-// K = 128 11.4 vs 12.3 at 16,400, 14.2 vs 13.3 at 41,000.
+// Up to 16,384 padded rows, 512 workgroups: at K = 512 two of them fit on a CU, and a
+// third round costs more than the panels' chain, one panel a CU up to 32,768
+// rows. Measured, us a launch against the panels, by padded rows with every length 25 (in
+// brackets 5 to 25): K = 512 -14 (-15) at 6,400, +1.5 (-12) at 12,800, -2 (-2) at 16,384,
+// +7 (-2) at 18,432, +16 (-3) at 25,600; K = 256 -3 (-6) at 10,000, -2 (-1) at 16,384,
+// +6 (0) at 20,000, +6 (-2) at 24,500; K = 128 -1 (-2.5) at 10,000, 0 (0) at 15,000, +1 (0)
+// at 20,000; K = 64 -0.4 at 10,000, 0.2 at 15,000 and 18,000.
 bool small_conv_wanted(const GemmArgs& a) {
   const int ch = a.K / kCW;
-  return a.Mmax <= 16384 + 32 * a.K && a.K % kCW == 0 && (ch == 1 || ch == 2 || ch == 4 || ch == 8);
+  return a.Mmax <= 16384 && a.K % kCW == 0 && (ch == 1 || ch == 2 || ch == 4 || ch == 8);
 }
 
 hipError_t launch_small_conv(const GemmArgs& a, const ConvIn& cv, const uint16_t* Ws, int ldws, hipStream_t s) {
@@ -386,8 +390,12 @@ hipError_t launch_small_conv(const GemmArgs& a, const ConvIn& cv, const uint16_t
   return hipGetLastError();
 }
 
-// Measured, against the panels: K = 512, N = 256 (four workgroups per 32 rows) 14.9
-// vs 22.3 us at 3,200 padded rows (400 workgroups), 25.8 vs 22.1 at 4,750.
+// Up to 416 workgroups of 32 x 64, by padded rows: with full lengths the second
+// workgroup on a CU (from 256) costs what shorter ones gain up to there. Measured,
+// us a launch against the panels, every length 25 (in brackets 5 to 25): K = 512, N =
+// 256 -8 (-6) at 200 workgroups, +4 (-7) at 312, +3 (-8) at 412, +5 (+4) at 500; K = 256, N = 128
+// -2 (-3) at 188, 0 (-2) at 312, -1 (+1) at 412, +5 (-1) at 626; K = 128, N = 128 -1 (-1) at 188, +2 (-1)
+// at 312, +2 (+1.5) at 412; K = 128, N = 64 -2 at 250, 0 (-1) at 416, +1.5 (0) at 625.
 bool small_f16acc_wanted(const GemmArgs& a) {
   const int ch = (a.K + kCW - 1) / kCW;
   return (int64_t)a.Mmax * a.N <= 416 * kRows * kCols && (ch == 1 || ch == 2 || ch == 4 || ch == 8);

@@ -983,3 +983,45 @@ def test_small_batches_keep_the_bits(shape, dtype, B):
         assert ((whole[:B] - part).abs() <= 2e-2 * whole.abs().max()).all()
     else:
         assert torch.equal(whole[:B], part)
+
+
+def _us_in_turn(fs, calls=20, rounds=9):
+    """The least time of a call of each of fs, timed in turn."""
+    for f in fs:
+        f()
+    torch.cuda.synchronize()
+    best = [float("inf")] * len(fs)
+    for _ in range(rounds):
+        for i, f in enumerate(fs):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(calls):
+                f()
+            b.record()
+            b.synchronize()
+            best[i] = min(best[i], a.elapsed_time(b) / calls * 1e3)
+    return best
+
+
+def test_conv_of_full_rows_leaves_the_small_kernel_in_time():
+    """25,600 rows with data, 512 channels: the kernel that their number gets
+    is not slower than the panels, which a larger bound on the rows gets (the
+    32-row workgroups took 1.4 times as long, in three rounds)."""
+    rows, L, E, N, bound = 25_600, 25, 512, 48, 40_000
+    print(f"conv of {rows} full rows", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    offs = torch.arange(rows // L + 1, dtype=torch.int32, device="cuda") * L
+    x = torch.randn(rows, 2 * E, generator=g, device="cuda")
+    w, b = torch.randn(E, 4, generator=g, device="cuda"), torch.randn(E, generator=g, device="cuda")
+    W = torch.randn(N, E, generator=g, device="cuda")
+    wsplit = torch.empty(3 * N * E, dtype=torch.int16, device="cuda")
+    tpos = torch.empty(bound, dtype=torch.uint8, device="cuda")
+    u, xdbl = torch.empty(bound, E, device="cuda"), torch.empty(bound, N, device="cuda")
+
+    def call(Mmax):
+        tb.check(tb.lib().tcl_test_xproj_conv_f32(rows // L, Mmax, E, N, offs.data_ptr(), x.data_ptr(), 2 * E,
+                                                  w.data_ptr(), b.data_ptr(), W.data_ptr(), wsplit.data_ptr(),
+                                                  tpos.data_ptr(), u.data_ptr(), xdbl.data_ptr(), tb._stream()))
+
+    us = _us_in_turn([lambda: call(rows), lambda: call(bound)])
+    assert us[0] < 1.15 * us[1], us
