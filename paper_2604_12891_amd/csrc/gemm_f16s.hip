@@ -517,9 +517,12 @@ hipError_t launch_f16s(const GemmArgs& a, const uint16_t* Wh, int ldwh, hipStrea
   if (grid <= 0) return hipSuccess;
   // two workgroups per CU: with fewer than two panels per CU the columns are
   // also split, up to 8 ways (each workgroup repeats its panel's prologue), or
-  // up to 32 ways while that is one workgroup per CU: in_proj at 8 programs of
-  // up to 25 tokens 15.9 us with 8 ways, 12.8 with 16, 11.5 with 32; at 64 17.2,
-  // 14.5 and 16.5; at 128 18.2, 19.5 and 19.1
+  // up to 32 ways while that is one workgroup per CU. In_proj of 1,024 columns,
+  // K = 256, us less than with 8 ways: up to 8 panels 32 ways 4 to 5 (16 ways 3);
+  // 9 panels 28 ways 2.4 (16 ways 2.8), 12 panels 21 ways 2.7 (32 ways 0.2), 16 panels 16
+  // ways 2.6, 18 panels 14 ways 1.3 (16 ways 1.5 more), 22 panels 11 ways 1.3 (14 ways 2.8
+  // more), 25 panels 10 ways 0 (16 ways 2 more). Of 512 columns 1 less up to 16 panels, of 256
+  // no difference
   const int nblk = (a.N + 31) / 32;
   const int cs = std::max(1, std::min(nblk, std::max(std::min(8, 512 / grid), std::min(32, 256 / grid))));
   const dim3 g(grid, cs);
