@@ -308,35 +308,39 @@ hipError_t dispatch_tile(const GemmArgsBF16& a, GemmBF16Tile tile, hipStream_t s
 }  // namespace
 
 GemmBF16Tile pick_gemm_bf16_tile(GemmBF16Kind kind, int Mmax, int N, int K) {
-  // Measured on MI355X (microseconds per call; rows: those with data, which
-  // Mmax = B * L exceeds by the padding, 1.67x at lengths U{L/5..L}). All tiles
-  // give the same bits; panels sum a row in another order. Below Mmax = 40,960,
-  // where a small model's training results would move with that order and
-  // panels gain nothing in a distillation step (1,265 us a pass against 1,258),
-  // tiles stay.
-  // Gathered input Linear (K = 164): N = 256, 1,000 rows 5.7 with 64x64 (8.2 with
-  // 128x64, 10.3 with 128x128), 10,000 9.4 (11.9, 12.7), 20,000 13.3 (15.9, 17);
-  // 128-row panels 21 vs 23.5 at 40,000 rows, 23.3 vs 33.5 at 61,600, 376 vs 591
-  // (391 for 256-row panels) at 983K.
-  // bf16 C, K <= 256 (in_proj N = 1024, K = 256): 64x64 while its tiles fit on
-  // the chip about once (1,000 rows 6.0 vs 6.8 for 64x128 and 9.5 for 128x128),
-  // then 64x128 (4,000 rows 9.1 vs 10.6 and 10.5; 10,000 17.7 vs 21 and 21),
-  // 128x128 (15,000 25.1 vs 25.9 for 64x128; 20,000 31.0 vs 32.4), 128-row panels
-  // (40,000 42.5 vs 54; 61,600 50 vs 82; 983K 896 vs 1489).
-  // Residual out_proj (no panel, K = 512): 64x64 up to 100,000 rows (10.8 vs 12.1
-  // for 128x64 at 10,000, 55 vs 57 and 66 for 128x128 at 100,000), 128x128
-  // above (99 vs 114 at 160,000). x_proj (N = 48) 64x64. The backward's fp32
-  // data gradients 64x64 at ~15,000 rows (8.3 vs 9.6 for 128x64 at N = 256, K =
-  // 128 with the residual, 10.2 vs 10.5 at N = 128, K = 512), 128x64 from 31,000
-  // (15.3 vs 13.5, 15.5 vs 15.0).
+  // Measured on MI355X, us a launch. The limits are on Mmax = B * L, which a
+  // batch's rows with data may be well below (0.6 of it at lengths U{L/5..L}), so each lies
+  // where neither full nor such batches lose much. All tiles give the same bits;
+  // panels sum in another order.
+  // Panels or tiles: in_proj (N = 1024, K = 256) with 128-row panels 29.5 vs 34.9 at
+  // 24,576 full rows, 32.7 vs 44.2 at 32,768, but 27.9 vs 25.7 at 16,384; the gathered input
+  // Linear (K = 164) 13.3 vs 14.0 at 24,576 and 20.3 vs 23.3 at 40,960 for N = 256, 8.6 vs
+  // 9.7 at 32,768, 10.9 vs 11.9 at 40,960 and 20.0 vs 20.4 at 98,304 for N = 64. Whole calls with
+  // panels against tiles, padded rows with lengths of 5 to 25 (in brackets all 25): a
+  // distillation step 1.03 (0.99) at 28,672, 1.01 (0.98) at 36,864, 1.00 (0.98) at 40,960, 0.99 (0.95)
+  // at 49,152, 0.95 (0.93) at 98,304; scoring, d 256, 1.01 (0.94) at 28,672, 0.98 (0.96) at
+  // 36,864, 0.93 (0.96) at 40,960, 0.91 (0.86) at 98,304. The line is where the step no longer
+  // loses, for both: a teacher's scores are the same inside a step and outside.
+  // bf16 C below it: 64x64 while its tiles fit on the chip about once (N = 1024, 1,000
+  // rows 6.0 vs 6.8 for 64x128 and 9.5 for 128x128), then 64x128 (4,000 rows 9.1 vs 10.6 and
+  // 10.5), 128x128 (20,000 31.0 vs 32.4). Gathered input below it: 64x64 (N = 256, 1,000
+  // rows 5.7 vs 8.2 for 128x64, 10,000 9.4 vs 11.9).
+  // Residual out_proj: K = 512, N = 256 64x64 26.7 vs 27.6 for 128x128 at 40,000 rows,
+  // 49.1 vs 52.7 at 90,000, 73.4 vs 75.9 at 131,072, then 93 vs 83 at 140,000 and 143 vs 124
+  // at 196,608. K = 256, N = 128 64x64 32.1 vs 34.9 (256-row panels 32.0) at 131,072, 61.9 vs
+  // 62.3 (64.5) at 260,000, 111 vs 110 (130) at 400,000, 278 vs 276 (290) at 1 M. x_proj
+  // (N = 48) 64x64.
+  // The backward's fp32 data gradients: 64x64 8.7 vs 10.0 for 128x64 at 16,384 rows (N =
+  // 256, K = 128 with the residual), 10.1 vs 11.2 (N = 128, K = 512); 128x64 14.2 vs 15.9 and
+  // 15.6 vs 15.7 at 32,768; 128x128 from 131,072 65.7 vs 67.9 (N = 128, K = 512), 56 vs 52
+  // (N = 256, K = 128).
   const bool bf16_out = kind == kNormF32toBF16 || kind == kBF16toBF16;
   const bool f32_grad = kind == kF32toF32 || kind == kF32ResidF32;
   if (N <= 64 && !(bf16_out || kind == kInputF32toF32)) return kB64x64;
   if (K <= 256 && (bf16_out || kind == kInputF32toF32) && Mmax >= 40960) return kBPanel128;
   if (bf16_out) return (int64_t)Mmax * N <= 1024 * 64 * 64 ? kB64x64 : Mmax < 24576 ? kB64x128 : kB128x128;
   if (f32_grad) return Mmax < 32768 && N <= 256 ? kB64x64 : Mmax < 131072 && N <= 256 ? kB128x64 : kB128x128;
-  if (K <= 256 && Mmax >= 262144) return kBPanel;
-  return N <= 256 && Mmax < 262144 ? kB64x64 : kB128x128;
+  return N <= 256 && Mmax < (K <= 256 ? 262144 : 131072) ? kB64x64 : kB128x128;
 }
 
 hipError_t launch_gemm_bf16(const GemmArgsBF16& a, GemmBF16Kind kind, int tile, hipStream_t s) {

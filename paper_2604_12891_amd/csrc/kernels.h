@@ -202,7 +202,7 @@ enum GemmBF16Tile {
   kB128x256 = 4,    // 8 wavefronts
   kB256x128 = 5,    // 8 wavefronts
   kB256x128W4 = 6,  // 4 wavefronts of 128x64 each
-  kBPanel = 7,      // row panels: 256 rows x all N per workgroup (K <= 256)
+  kBPanel = 7,      // row panels: 256 rows x all N per workgroup (K <= 256); only when asked for
   kBPanel128 = 8,   // row panels of 128 rows (32 per wavefront)
   kNumGemmBF16Tiles = 9
 };

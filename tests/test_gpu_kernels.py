@@ -322,9 +322,9 @@ def test_gemm_bf16_variants(kind, tile):
 @pytest.mark.parametrize("kind,N,K,panel", [("norm", 1024, 256, 40960), ("gather", 256, 164, 40960),
                                             ("f32a", 256, 128, None), ("resid", 256, 512, None)])
 def test_gemm_bf16_model_tiles_keep_the_bits(kind, N, K, panel, M):
-    """Around each size where the model's tile choice changes: the chosen
-    kernel gives the bits of the 128x128 tiles, or of the 128-row panels where
-    those are chosen."""
+    """Around the sizes up to 40,960 rows where the model's tile choice changes
+    (those above are below): the chosen kernel gives the bits of the 128x128
+    tiles, or of the 128-row panels where those are chosen."""
     print(f"gemm_bf16 model tile kind={kind} M={M}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(M + N)
     A = torch.randn(M, K, generator=g, device="cuda")
@@ -1025,3 +1025,44 @@ def test_conv_of_full_rows_leaves_the_small_kernel_in_time():
 
     us = _us_in_turn([lambda: call(rows), lambda: call(bound)])
     assert us[0] < 1.15 * us[1], us
+
+
+@pytest.mark.parametrize("kind,N,K,M,same_as", [
+    ("f32a", 256, 128, 32_767, 0), ("f32a", 256, 128, 32_768, 0), ("f32a", 128, 512, 131_071, 0),
+    ("f32a", 128, 512, 131_072, 0), ("f32a_resid", 256, 128, 131_071, 0), ("f32a_resid", 256, 128, 131_072, 0),
+    ("resid", 256, 512, 131_071, 0), ("resid", 256, 512, 131_072, 0), ("resid", 128, 256, 262_143, 0),
+    ("resid", 128, 256, 262_144, 0), ("gather", 64, 164, 40_959, 0), ("gather", 64, 164, 40_960, 8),
+    ("norm", 256, 64, 40_959, 0), ("norm", 256, 64, 40_960, 8)])
+def test_gemm_bf16_model_tiles_at_the_other_limits(kind, N, K, M, same_as):
+    """The limits that are not among the sizes of the test above: the fp32
+    gradients' 32,768 and 131,072 rows, the residual out_proj's 131,072 (K =
+    512) and 262,144 (K = 256), and the panels' 40,960 at narrow outputs."""
+    print(f"gemm_bf16 limit kind={kind} N={N} K={K} M={M}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    A = torch.randn(M, K, generator=g, device="cuda")
+    W = torch.zeros(N, (K + 7) // 8 * 8, dtype=torch.bfloat16, device="cuda")
+    W[:, :K] = torch.randn(N, K, generator=g, device="cuda").bfloat16()
+    kw = {"f32a": dict(kind=tb.GEMM_BF16_F32A), "f32a_resid": dict(kind=tb.GEMM_BF16_F32A_RESID),
+          "resid": dict(kind=tb.GEMM_BF16_RESID),
+          "norm": dict(kind=tb.GEMM_BF16_NORM, gain=torch.rand(K, generator=g, device="cuda") + 0.5),
+          "gather": dict(kind=tb.GEMM_BF16_GATHER, bias=torch.randn(N, generator=g, device="cuda"),
+                         offs=torch.arange(M + 1, dtype=torch.int32, device="cuda"))}[kind]
+    A = A.bfloat16() if kind == "resid" else A.view(M, 1, K) if kind == "gather" else A
+    start = torch.randn(M, N, generator=g, device="cuda")
+    a, b = (tb.gemm_bf16(A, W, out=start.clone() if kind in ("resid", "f32a_resid") else None, tile=t, **kw)
+            for t in (-1, same_as))
+    torch.cuda.synchronize()
+    assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("M", [160_000, 240_000])
+def test_out_proj_of_full_rows_has_the_faster_tiles(M):
+    """The bf16 out_proj of the 256-wide model, every row with data: the tile
+    that is chosen is not slower than 128x128 (64x64 took 1.11 to 1.15 times as
+    long)."""
+    print(f"out_proj of {M} full rows", flush=True)
+    A = torch.randn(M, 512, device="cuda").bfloat16()
+    W = torch.randn(256, 512, device="cuda").bfloat16()
+    out = torch.zeros(M, 256, device="cuda")
+    us = _us_in_turn([lambda t=t: tb.gemm_bf16(A, W, out=out, tile=t, kind=tb.GEMM_BF16_RESID) for t in (-1, 0)])
+    assert us[0] < 1.06 * us[1], us
