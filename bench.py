@@ -395,9 +395,10 @@ def bench_progressive(args, w):
                    "f32_matmul": args.f32_matmul, "encoder": [w.model.F, *w.model.enc_hidden, w.model.d_model],
                    "d_state": w.model.d_state, "n_layers": w.model.n_layers,
                    "lengths": f"uniform {w.len_lo}..{w.len_hi}", "valid_tokens": M_v,
-                   # the library picks the sequential scan when the batch alone fills the GPU
-                   # (B * d_inner / 64 >= 1024 wavefronts) and the chunked two-level scan below
-                   "scan": "chunked two-level" if "scan_chunked" in kernels else "sequential"},
+                   # the small-batch scan up to 1024 groups of 64 channels of a program; the
+                   # chunked two-level scan is for dt_ranks that it has no instance for
+                   "scan": "chunked two-level" if "scan_chunked" in kernels else
+                           "small-batch" if w.B * ((w.model.d_inner + 63) // 64) <= 1024 else "sequential"},
         "wall_ms_per_step": wall * 1e3 / args.steps, "roofline": roof,
         "kernels": {k: {kk: (round(vv, 5) if isinstance(vv, float) else vv) for kk, vv in e.items()}
                     for k, e in kernels.items()},
@@ -625,7 +626,7 @@ def bench_consumers(args):
 
 
 def scan_sweep(args):
-    """Time the sequential scan and the chunked two-level scan on their own
+    """Time the sequential (or small-batch) scan and the chunked two-level scan on their own
     (kernel-level entry point, HIP events on the launch stream) for programs
     of length 64..256, batch sizes from the long-sequence workload (8192)
     down to 16. Prints one JSON line."""
@@ -661,7 +662,7 @@ def scan_sweep(args):
             e1.record()
             torch.cuda.synchronize()
             ms = e0.elapsed_time(e1) / reps
-            key = "sequential" if chunks == 0 else f"chunked{chunks}"
+            key = f"chunked{chunks}" if chunks else "small_batch" if B * E // 64 <= 1024 else "sequential"
             rec[key + "_ms"] = round(ms, 5)
             rec[key + "_GBps"] = round(rows * (3 * E * 4 + (R + 2 * N) * 4) / (ms * 1e-3) / 1e9, 1)
         out.append(rec)
@@ -723,10 +724,9 @@ def other_workloads(args) -> dict:
         out[name] = {"value": w.B / (ms * 1e-3), "unit": "programs/s", "ms_per_step": ms, "dtype": w.dtype,
                      "graph_replay": graph,
                      "B": w.B, "L": w.L, "valid_tokens": int(lengths.sum()), "steps": steps,
-                     # the library's rule: the chunked two-level scan only for L >= 64 with
-                     # fewer than 1024 wavefronts of (program, 64 channels)
-                     "scan": ("chunked two-level" if w.L >= 64 and waves < 1024 else "sequential")
-                             + f" ({waves} wavefronts)"}
+                     # the library's rule at these dt_ranks (4, 8, 16): the small-batch scan
+                     # up to 1024 groups of 64 channels of a program
+                     "scan": ("small-batch" if waves <= 1024 else "sequential") + f" ({waves} groups of 64 channels)"}
         del model, Xd, Ld, ws, o
         torch.cuda.empty_cache()
     w = wl.WORKLOADS["distill_B1024_L25_t256_s128_bf16"]
@@ -959,9 +959,10 @@ def main():
                    "encoder": [w.model.F, *w.model.enc_hidden, w.model.d_model],
                    "decoder": [w.model.d_model, w.model.head_hidden, *([w.model.dec_hidden2] if w.model.dec_hidden2 else []), 1],
                    "lengths": f"uniform {w.len_lo}..{w.len_hi}", "valid_tokens": M_v,
-                   # the library picks the sequential scan when the batch alone fills the GPU
-                   # (B * d_inner / 64 >= 1024 wavefronts) and the chunked two-level scan below
-                   "scan": "chunked two-level" if "scan_chunked" in kernels else "sequential"},
+                   # the small-batch scan up to 1024 groups of 64 channels of a program; the
+                   # chunked two-level scan is for dt_ranks that it has no instance for
+                   "scan": "chunked two-level" if "scan_chunked" in kernels else
+                           "small-batch" if w.B * ((w.model.d_inner + 63) // 64) <= 1024 else "sequential"},
         "wall_ms_per_step": wall * 1e3 / args.steps,
         "roofline": roof,
         "roofline_single_stream": roof1,

@@ -573,7 +573,8 @@ def offsets(lengths, L, ord=None, stream=None):
 
 
 def scan_f32(offs, u, xdbl, z, W_dt, b_dt, A_log, D, out, ldz=None, stream=None, chunks=0):
-    """chunks = 0: sequential scan; 1..8: chunked two-level scan."""
+    """chunks = 0: the sequential or the small-batch scan, as tcl_score chooses;
+    1..8: chunked two-level scan."""
     B = offs.numel() - 1
     E = u.shape[1]
     N = A_log.shape[1]

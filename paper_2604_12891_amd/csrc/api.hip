@@ -1151,8 +1151,9 @@ TCL_API tcl_status tcl_test_scan_f32(int32_t B, int32_t E, int32_t N, int32_t R,
                                      float* d_out, void* stream) {
   if (B <= 0 || E <= 0 || ldz < E) return fail(TCL_ERR_INVALID_ARG, "bad sizes");
   if (chunks < 0 || chunks > 8) return fail(TCL_ERR_INVALID_ARG, "chunks must be in [0, 8]");
-  if (N != 16) return fail(TCL_ERR_UNSUPPORTED, "d_state must be 16");
-  if (R % 4 || R <= 0 || R > 32) return fail(TCL_ERR_UNSUPPORTED, "dt_rank must be 4..32, step 4");
+  if (N != 16 && (N != 8 || chunks > 0)) return fail(TCL_ERR_UNSUPPORTED, "d_state must be 16, or 8 with chunks 0");
+  if (R % 4 || R <= 0 || R > (N == 16 ? 32 : 16) || (N == 8 && R == 12))
+    return fail(TCL_ERR_UNSUPPORTED, "dt_rank must be 4..32, step 4 (4, 8 or 16 with d_state 8)");
   if (!d_offs || !d_u || !d_xdbl || !d_z || !d_W_dt || !d_b_dt || !d_A_log || !d_D || !d_out)
     return fail(TCL_ERR_INVALID_ARG, "NULL device pointer");
   if (chunks > 0)

@@ -279,7 +279,8 @@ hipError_t launch_scan(int B, int E, int N, int R, const int* offs, const T* u, 
 // The same scan as a chunked two-level scan: each program's tokens are split
 // into `chunks` (1..8) that are scanned concurrently and stitched through
 // their affine summaries. scan_chunks_for picks the chunk count the batch
-// needs to fill the GPU (0: the sequential kernel already does).
+// needs to fill the GPU (0: the sequential kernel already does). N is 16; bf16
+// has the ranks that scan_small_wanted does not take.
 template <typename T>
 hipError_t launch_scan_chunked(int B, int E, int N, int R, int chunks, const int* offs, const T* u,
                                const float* xdbl, const T* z, int ldz, const float* W_dt,

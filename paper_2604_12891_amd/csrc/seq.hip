@@ -920,28 +920,32 @@ hipError_t launch_scan_chunked(int B, int E, int N, int R, int chunks, const int
                                const float* b_dt, const float* A_log, const float* D, T* out,
                                hipStream_t s) {
   if (B <= 0) return hipSuccess;
-  if ((N != 16 && N != 8) || chunks < 1 || chunks > 8) return hipErrorInvalidValue;
+  if (N != 16 || chunks < 1 || chunks > 8) return hipErrorInvalidValue;
   dim3 grid(B, (E + 63) / 64);
   const size_t shm = (size_t)chunks * 64 * 2 * N * sizeof(float);
+  // The models come here with the ranks that the small-batch scan has no
+  // instance for; the others are for fp32, where the kernel's own entry point takes them.
 #define TCL_SCANC(NN, RR)                                                                      \
   hipLaunchKernelGGL((scan_chunked_kernel<T, NN, RR>), grid, dim3(64 * chunks), shm, s, offs, E, u, \
                      xdbl, z, ldz, W_dt, b_dt, A_log, D, out)
-  switch (N * 100 + R) {
-    case 1604: TCL_SCANC(16, 4); break;
-    case 1608: TCL_SCANC(16, 8); break;
-    case 1612: TCL_SCANC(16, 12); break;
-    case 1616: TCL_SCANC(16, 16); break;
-    case 1620: TCL_SCANC(16, 20); break;
-    case 1624: TCL_SCANC(16, 24); break;
-    case 1628: TCL_SCANC(16, 28); break;
-    case 1632: TCL_SCANC(16, 32); break;
-    case 804: TCL_SCANC(8, 4); break;
-    case 808: TCL_SCANC(8, 8); break;
-    case 816: TCL_SCANC(8, 16); break;
-    default: return hipErrorInvalidValue;
+  switch (R) {
+    case 12: TCL_SCANC(16, 12); return hipGetLastError();
+    case 20: TCL_SCANC(16, 20); return hipGetLastError();
+    case 24: TCL_SCANC(16, 24); return hipGetLastError();
+    case 28: TCL_SCANC(16, 28); return hipGetLastError();
+    case 32: TCL_SCANC(16, 32); return hipGetLastError();
+    default: break;
+  }
+  if constexpr (sizeof(T) == 4) {
+    switch (R) {
+      case 4: TCL_SCANC(16, 4); return hipGetLastError();
+      case 8: TCL_SCANC(16, 8); return hipGetLastError();
+      case 16: TCL_SCANC(16, 16); return hipGetLastError();
+      default: break;
+    }
   }
 #undef TCL_SCANC
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
 int scan_chunks_for(int B, int E, int L) {
@@ -949,6 +953,7 @@ int scan_chunks_for(int B, int E, int L) {
   // MI355X at L = 256, E = 512: the sequential scan wins from 2048 wavefronts
   // up (B >= 256), the chunked scan from 512 down (1.7x at B = 64 with 4
   // chunks, 2.3x at B = 16 with 4-8). Aim for >= 2048 wavefronts in total.
+  // (Ranks 4, 8 and 16 have the small-batch scan there, at every L.)
   const int64_t waves = (int64_t)B * ((E + 63) / 64);
   if (L < 64 || waves >= 1024) return 0;
   int c = 2;
@@ -958,7 +963,11 @@ int scan_chunks_for(int B, int E, int L) {
 
 // Whether a batch gets the small-batch scan: up to 1,024 workgroups. At E = 512, L =
 // 25: 14.8 us vs 19.7 with 1,024 of them (bf16 14.1 vs 18.8), bf16 20.8 vs 19.2 with
-// 1,600; E = 256 22.9 vs 19.1 with 2,048.
+// 1,600; E = 256 22.9 vs 19.1 with 2,048. It takes the chunked scan's place however long
+// the programs are: scoring calls of 16 to 1,024 groups at L = 64 to 2,048, both types, take
+// 0.59 to 0.87 of the time with it (L = 2,048, d 256, fp32: one program 2,644 -> 1,969 us,
+// 64 programs 7,071 -> 4,559; L = 1,024, 128 programs 5,185 -> 4,268; L = 256, 128 programs
+// 1,336 -> 1,166): two of its workgroups, 76 KB each, fit on a CU, so 1,024 run in two rounds.
 bool scan_small_wanted(int B, int E, int N, int R) {
   return (int64_t)B * ((E + 63) / 64) <= 1024 && (N == 16 || N == 8) && (R == 4 || R == 8 || R == 16);
 }

@@ -483,7 +483,7 @@ def test_xproj_conv_rejects_unsupported():
 @pytest.mark.parametrize("L", [1, 25, 70, 256])
 @pytest.mark.parametrize("chunks", [0, 1, 2, 3, 5, 8])
 def test_scan_f32(R, L, chunks):
-    """chunks = 0: sequential scan; > 0: the chunked two-level scan."""
+    """chunks = 0: the small-batch scan; > 0: the chunked two-level scan."""
     N, E = 16, 320
     rng = np.random.default_rng(R * 100 + L)
     lengths = rng.integers(1, L + 1, size=11).astype(np.int32)
@@ -512,6 +512,14 @@ def test_scan_f32(R, L, chunks):
     scale = np.sqrt(np.mean(expect ** 2))
     err = np.abs(got - expect)
     assert np.all(err <= 1e-4 * (np.abs(expect) + scale)), float(np.max(err / (np.abs(expect) + scale)))
+
+
+@pytest.mark.parametrize("R", [8, 12, 20, 24, 28, 32])
+@pytest.mark.parametrize("L,chunks", [(70, 0), (70, 2), (256, 8)])
+def test_scan_f32_other_ranks(R, L, chunks):
+    """The remaining ranks, with chunks 0 the small-batch scan (8) and the
+    sequential one (the others)."""
+    test_scan_f32(R, L, chunks)
 
 
 def test_scan_chunked_at_long_sequence_shape():
@@ -936,12 +944,13 @@ def test_small_f16acc_matches_the_panels(M, N, K, mode):
 
 @pytest.mark.parametrize("R", [4, 8, 16])
 @pytest.mark.parametrize("L", [1, 15, 16, 17, 50])
-def test_small_scan_matches_the_general_scan(R, L):
+@pytest.mark.parametrize("N", [8, 16])
+def test_small_scan_matches_the_general_scan(R, L, N):
     """The small-batch scan (chunks of 16 tokens, four lanes per channel)
     against scan_kernel: the same programs, first on their own, then followed
     by as many of one token as it takes. The same bits."""
-    N, E, B = 16, 320, 9
-    print(f"small scan R={R} L={L}", flush=True)
+    E, B = 320, 9
+    print(f"small scan R={R} L={L} N={N}", flush=True)
     rng = np.random.default_rng(R * 10 + L)
     lengths = rng.integers(1, L + 1, size=B).astype(np.int32)
     lengths[0] = L

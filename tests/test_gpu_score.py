@@ -82,35 +82,61 @@ def test_long_sequences_full_batch(f32_matmul):
     assert_scores_match(g, o, "f32", w.name)
 
 
-def test_long_sequences_chunked_scan_full_shape():
-    """The long-sequence workload's own programs through the chunked
-    two-level scan: a batch of 96 of them (sampled with the first and last,
-    the shortest and the longest) is too small to fill the GPU with one
-    thread per (program, channel), so tcl_score scans each program in
-    concurrent chunks; scores against the oracle's stored ones."""
+def test_long_sequences_small_batch_full_shape():
+    """The long-sequence workload's own programs through the small-batch
+    scan: a batch of 96 of them (sampled with the first and last, the shortest
+    and the longest) is too small to fill the GPU with one thread per
+    (program, channel); scores against the oracle's stored ones."""
     w = wl.WORKLOADS["score_B8192_L256_d256_f32"]
     blob, X, lengths = wl.make_workload(w.name)
     o = golden_scores(w.name, blob, X, lengths)
     idx = _sample(lengths, 92, seed=3)
     assert {0, w.B - 1} <= set(idx.tolist())
-    print(f"tcl_score {w.name} {len(idx)} sampled programs (chunked scan)", flush=True)
+    print(f"tcl_score {w.name} {len(idx)} sampled programs (small-batch scan)", flush=True)
     g = _score(_model(w.model, blob), X[idx], lengths[idx])
-    assert_scores_match(g, o[idx], "f32", w.name + " chunked")
+    assert_scores_match(g, o[idx], "f32", w.name + " small batch")
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_long_sequences_small_batch(dtype):
     """A batch too small to fill the GPU with one thread per (program,
-    channel): tcl_score runs the chunked two-level scan here."""
+    channel): tcl_score runs the small-batch scan here."""
     w = wl.WORKLOADS["score_B8192_L256_d256_f32"]
     blob, X, lengths = wl.make_workload(w.name, B=6, perturb=True)
     lengths[0], lengths[1] = 256, 64
     X[np.arange(256)[None, :] >= lengths[:, None]] = 0
     if dtype == "bf16":
         blob = wl.round_to_bf16(blob)
-    print(f"tcl_score B=6 L=256 {dtype} (chunked scan)", flush=True)
+    print(f"tcl_score B=6 L=256 {dtype} (small-batch scan)", flush=True)
     g = _score(_model(w.model, blob, dtype), X, lengths)
     assert_scores_match(g, oracle_scores(blob, X, lengths, w.model), dtype, "small batch, long sequences")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("dt_rank", [12, 32])
+def test_few_long_programs_take_the_chunked_scan(dt_rank, dtype):
+    """Long programs of a model whose dt_rank the small-batch scan has no
+    instance for: a batch too small to fill the GPU takes the chunked
+    two-level scan, 8 chunks for two programs and 2 for 255 of them (1,020
+    groups of 64 channels); one program more the sequential one. Against the
+    oracle, and the kernel's name in the timing report."""
+    shape = wl.ModelShape(F=24, d_model=64, d_inner=256, dt_rank=dt_rank, n_layers=2, head_hidden=64)
+    rng = np.random.default_rng(dt_rank)
+    blob = wl.init_params(shape, rng, perturb=True)
+    if dtype == "bf16":
+        blob = wl.round_to_bf16(blob)
+    m = _model(shape, blob, dtype)
+    X, lengths = wl.make_inputs(256, 70, shape.F, 1, 70, rng)
+    for B, L, kernel in ((2, 150, "scan_chunked"), (255, 70, "scan_chunked"), (256, 70, "scan")):
+        print(f"tcl_score dt_rank={dt_rank} {dtype} B={B} L={L} ({kernel})", flush=True)
+        x, n = (X, lengths) if L == 70 else wl.make_inputs(B, L, shape.F, 90, L, rng)
+        m.timing_reset()
+        m.timing(True)
+        g = _score(m, x[:B], n[:B])
+        m.timing(False)
+        ran = {k for k, (_, launches) in m.timing_report().items() if launches}
+        assert kernel in ran and not ({"scan", "scan_chunked"} - {kernel}) & ran, ran
+        assert_scores_match(g, oracle_scores(blob, x[:B], n[:B], shape), dtype, f"dt_rank {dt_rank} B={B}")
 
 
 @pytest.mark.parametrize("perturb", [False, True])

@@ -84,8 +84,8 @@ def test_variant_pieces_on_other_shapes(dtype):
         assert_scores_match(g, oracle_scores(blob, X, lengths, shape), dtype, f"piece {i}")
 
 
-def test_paper_model_long_sequences_chunked_scan():
-    """A few long programs: the chunked scan with d_state 8."""
+def test_paper_model_long_sequences_small_batch():
+    """A few long programs: the small-batch scan with d_state 8."""
     shape = wl.PAPER_GPU
     rng = np.random.default_rng(7)
     blob = wl.init_params(shape, rng, perturb=True)
