@@ -596,15 +596,15 @@ def bench_consumers(args):
     steps = max(2, args.steps // 10)
     ms = timed(lambda: tb.rdu_select(sc, op, n_ops, init, n_sel, workspace=ws), steps)
     per_sel = ms / n_sel
-    nbytes = N * 16  # per selection: score, operator type and running distance of every program, read once
+    nbytes = N * 8  # what a call cannot do without: score and operator type of every program, read once
     res["rdu_select"] = {"ms_per_call": ms, "ms_per_selection": per_sel, "selections_per_s": 1e3 / per_sel,
                          "config": f"pool {N}, {n_ops} operator types, {n_init} initial, {n_sel} selections",
-                         "roofline": {"bound": "hbm", "achieved": nbytes / (per_sel * 1e-3) / 1e9,
+                         "roofline": {"bound": "hbm", "achieved": nbytes / (ms * 1e-3) / 1e9,
                                       "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                                      "frac": nbytes / (per_sel * 1e-3) / 1e9 / HBM_PEAK_GBS, "traffic": None,
-                                      "bytes_per_selection": nbytes,
-                                      "note": "includes the setup pass (normalisation, budgets, distances "
-                                              "to the initial set) amortised over the selections"}}
+                                      "frac": nbytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, "traffic": None,
+                                      "bytes_per_call": nbytes,
+                                      "note": "a call is a chain of launches, most of them on a short list of "
+                                              "candidates; a few read the whole pool (16 bytes a program)"}}
     cpu = None
     if not args.no_cpu_baseline:
         from oracle import select as osel
@@ -626,19 +626,21 @@ def bench_consumers(args):
 
 
 def scan_sweep(args):
-    """Time the sequential (or small-batch) scan and the chunked two-level scan on their own
-    (kernel-level entry point, HIP events on the launch stream) for programs
-    of length 64..256, batch sizes from the long-sequence workload (8192)
-    down to 16. Prints one JSON line."""
+    """Time the scan that tcl_score gives a batch when it does not chunk it and
+    the chunked two-level scan on their own (kernel-level entry point, HIP
+    events on the launch stream) for programs of length 64..256, batch sizes
+    from the long-sequence workload (8192) down to 16: at dt_rank 16, where the
+    small-batch scan takes up to 1,024 groups of 64 channels, and at 12, which
+    it has no instance for. Prints one JSON line."""
     import numpy as np
     import torch
 
     from paper_2604_12891_amd import binding as tb
 
-    E, N, R, L = 512, 16, 16, 256
+    E, N, L = 512, 16, 256
     rng = np.random.default_rng(7)
     out = []
-    for B in (8192, 1024, 256, 64, 16):
+    for R, B in [(R, B) for R in (16, 12) for B in (8192, 1024, 256, 128, 64, 16)]:
         lengths = rng.integers(64, L + 1, size=B).astype(np.int32)
         rows = int(lengths.sum())
         offs = torch.from_numpy(np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)).cuda()
@@ -650,7 +652,7 @@ def scan_sweep(args):
         A_log = torch.log(torch.arange(1, N + 1, device="cuda", dtype=torch.float32)).repeat(E, 1)
         D = torch.ones(E, device="cuda")
         res = torch.empty_like(u)
-        rec = {"B": B, "valid_tokens": rows}
+        rec = {"dt_rank": R, "B": B, "valid_tokens": rows}
         for chunks in (0, 2, 4, 8):
             for _ in range(3):
                 tb.scan_f32(offs, u, xdbl, z, W_dt, b_dt, A_log, D, res, chunks=chunks)
@@ -662,7 +664,8 @@ def scan_sweep(args):
             e1.record()
             torch.cuda.synchronize()
             ms = e0.elapsed_time(e1) / reps
-            key = f"chunked{chunks}" if chunks else "small_batch" if B * E // 64 <= 1024 else "sequential"
+            small = R == 16 and B * E // 64 <= 1024
+            key = f"chunked{chunks}" if chunks else "small_batch" if small else "sequential"
             rec[key + "_ms"] = round(ms, 5)
             rec[key + "_GBps"] = round(rows * (3 * E * 4 + (R + 2 * N) * 4) / (ms * 1e-3) / 1e9, 1)
         out.append(rec)

@@ -537,9 +537,12 @@ __global__ __launch_bounds__(kST) void rdu_mark_kernel(int N, const int* __restr
 // (759 / 1,958 / 3,625).
 // The arithmetic per candidate is the same in both, and ties go to the lower
 // index, so the selection is too. The call over 8.65 M programs with 1,024
-// initial ones, 64 selections: 3.62 ms with passes over the whole pool only,
-// 1.13 ms now (three such passes and 62 launches of 8 us on lists, bound by
-// the latency of a launch's chain of loads, block reductions and arrival).
+// initial ones, 64 selections: 3.6 ms with passes over the whole pool only,
+// 1.10 to 1.20 ms now. Of that, in one traced call, five passes over the pool of 59 to 93
+// us (the first samples; the others also collect, and fold in the up to 20 labels
+// since the one before) take 392 us, 62 launches on lists of 6 to 9 us, bound by the
+// latency of a chain of loads, block reductions and arrival, 507, the setup 115 and nine
+// launches with nothing left to do 40.
 constexpr int kRduUnroll = 4;
 constexpr int kRduList = 32768;       // room of the short list
 constexpr double kRiseMargin = 1e-12;  // far above the rounding of u_s and of its change (a few 1e-16)
