@@ -950,9 +950,10 @@ hipError_t launch_scan_chunked(int B, int E, int N, int R, int chunks, const int
 
 int scan_chunks_for(int B, int E, int L) {
   // One thread per (program, channel) gives B*E/64 wavefronts. Measured on
-  // MI355X at L = 256, E = 512: the sequential scan wins from 2048 wavefronts
-  // up (B >= 256), the chunked scan from 512 down (1.7x at B = 64 with 4
-  // chunks, 2.3x at B = 16 with 4-8). Aim for >= 2048 wavefronts in total.
+  // MI355X at lengths 64..256, E = 512, R = 12: the sequential scan wins from 2048
+  // wavefronts up (0.16 ms vs 0.25 with 4 chunks), the chunked scan from 1024 down
+  // (0.137 with 4 chunks vs 0.154; 512 0.100 vs 0.142; 128 0.052 with 8 vs 0.123). Aim
+  // for >= 2048 wavefronts in total.
   // (Ranks 4, 8 and 16 have the small-batch scan there, at every L.)
   const int64_t waves = (int64_t)B * ((E + 63) / 64);
   if (L < 64 || waves >= 1024) return 0;
