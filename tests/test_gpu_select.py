@@ -237,13 +237,14 @@ def _rdu_bytes_without_list(N, n_ops):
 
 
 @pytest.mark.parametrize("N", [200_003, 600_001])
-@pytest.mark.parametrize("kind", ["normal", "coarse", "ties", "constant", "lognormal", "sorted", "budgets", "nan"])
+@pytest.mark.parametrize("kind", ["normal", "coarse", "ties", "constant", "lognormal", "sorted", "budgets", "nan",
+                                  "few", "many_initial"])
 def test_rdu_select_without_room_for_the_list(N, kind):
     """A workspace of the size that large pools needed before they had the
     short list is accepted, nothing past its end is written, and the
     selections are those with the list: 200 of them, so that lists come to
     little, are waited for and tried again; one byte less is refused."""
-    n_ops, n_init, n_sel = 9, 48, 200
+    n_ops, n_init, n_sel = 9, 9_000 if kind == "many_initial" else 48, 200
     print(f"rdu without room {kind} N={N}", flush=True)
     s, op, init = _rdu_case(N, n_ops, n_init, 500)
     rng = np.random.default_rng(501)
@@ -256,8 +257,10 @@ def test_rdu_select_without_room_for_the_list(N, kind):
         s = np.exp(10 * s).astype(np.float32)
     elif kind == "sorted":
         s = np.sort(s)
-    elif kind == "budgets":  # most programs of one type, and types that no program may have
+    elif kind == "budgets":  # most programs of one type, some of types that are never selected
         op = np.where(rng.random(N) < 0.9, 0, rng.integers(-2, n_ops + 2, N)).astype(np.int32)
+    elif kind == "few":  # the pool runs out: most programs are of no type, and each type's budget is one
+        op = np.where(rng.random(N) < 0.999, -1, op).astype(np.int32)
     elif kind == "nan":
         s[np.setdiff1d(rng.integers(0, N, N // 50), init)] = np.nan
     s, op, init = _dev(s, torch.float32), _dev(op, torch.int32), _dev(init, torch.int32)
@@ -270,6 +273,7 @@ def test_rdu_select_without_room_for_the_list(N, kind):
     plain, c = tb.rdu_select(s, op, n_ops, init, n_sel, workspace=buf[:least])
     torch.cuda.synchronize()
     assert torch.equal(count, c) and torch.equal(listed, plain)
+    assert (int(c) < n_sel) == (kind in ("few", "budgets")), int(c)
     assert (buf[least:] == 0x5A).all() and not (buf[:least] == 0x5A).all()
     st = tb.lib().tcl_rdu_select(N, s.data_ptr(), op.data_ptr(), n_ops, init.data_ptr(), n_init, n_sel,
                                  plain.data_ptr(), c.data_ptr(), buf.data_ptr(), least - 1, None)
